@@ -512,8 +512,8 @@ logo_status logo_branch_transform(int64_t n_tokens, int32_t num_heads, int32_t h
  *   Everything else as for logo_attn_fwd (there is no q_g argument).
  *   ws >= logo_workspace_bytes(p, LOGO_ENTRY_FWD_QPHI, sel_capacity) bytes,
  *   256-byte aligned: LOGO_ENTRY_FWD's workspace plus, for LP, a permuted
- *   copy of A (2 Hq d^2 bytes) that the local-branch launch writes for the
- *   global one.
+ *   copy of A (2 Hq d^2 bytes) that the selection launch writes for the
+ *   global branch.
  */
 logo_status logo_attn_fwd_qphi(const logo_problem *p, const logo_bf16 *q, const logo_bf16 *k,
                                const logo_bf16 *v, logo_phi_kind q_phi, const logo_bf16 *A,

@@ -261,17 +261,9 @@ struct ItemL {
     int ep_rank[RG];
 };
 
-// Column of the LP matrix that row r of its permuted copy holds: bits 2 and 3
-// of r (within its 32-row block) swapped.  With A'[h][r][k] = A[h][k][perm(r)]
-// as the A operand of the 32x32x16 MFMA and a lane's Q fragments as the B
-// operand, accumulator element 8 j + e of lane (g, m) is output channel
-// 16 j + 8 g + e of its 32-channel block for query row m -- the layout of the
-// B operand of the next product, so the rounded result replaces the
-// fragments directly.
-__device__ __forceinline__ int lp_perm(int r) { return (r & ~0xC) | ((r & 4) << 1) | ((r & 8) >> 1); }
-
 // Q^G = phi(Q) on the selected rows as the global kernel loads them (Eq.
-// branch-transform): LP q A_h (bf16 MFMA, fp32 accumulation) or SO
+// branch-transform): LP q A_h (bf16 MFMA, fp32 accumulation; A_h from the
+// permuted copy that the selection launch wrote, see lp_perm) or SO
 // q * s_h + b_h (fp32), one bf16 rounding each.
 template <int D>
 __device__ __forceinline__ void apply_qphi(const AttnArgs &a, int head,
@@ -327,21 +319,6 @@ __device__ __forceinline__ void apply_qphi(const AttnArgs &a, int head,
                     qf[rg][ks][e + 1] = v[1];
                 }
         }
-    }
-}
-
-// The permuted copy of one head's LP matrix (see lp_perm), 16 bytes per
-// thread and step: A'[r][k0 .. k0+7] gathers column lp_perm(r) of rows
-// k0 .. k0+7 of A.
-template <int D, int NT>
-__device__ __forceinline__ void permute_lp_head(const uint16_t *A, uint16_t *Ap, int head) {
-    const uint16_t *src = A + (int64_t)head * D * D;
-    uint16_t *dst = Ap + (int64_t)head * D * D;
-    for (int c = threadIdx.x; c < D * D / 8; c += NT) {
-        const int r = c / (D / 8), k0 = (c % (D / 8)) * 8;
-        const uint16_t *sc = src + k0 * D + lp_perm(r);
-        auto pair = [&](int e) { return (uint32_t)sc[e * D] | ((uint32_t)sc[(e + 1) * D] << 16); };
-        *(u32x4 *)(dst + r * D + k0) = u32x4{pair(0), pair(2), pair(4), pair(6)};
     }
 }
 
@@ -1086,27 +1063,16 @@ void attn_kernel(const AttnArgs a) {
         const int wid = blockIdx.x;
         if constexpr (EPI != kEpiRaw) {
             // The fused layer's local launch: after the item_stride
-            // persistent workgroups come one that builds the global branch's
-            // work table (its LDS holds the table) and, for a global branch
-            // with an LP query transform, one per head that writes the
-            // permuted copy of its matrix.  Being last, they take CUs that
-            // the first workgroups to finish leave free, and no item
-            // workgroup waits for them.
+            // persistent workgroups comes one that builds the global branch's
+            // work table (its LDS holds the table).  Being last, it takes a
+            // CU that the first workgroup to finish leaves free, and no item
+            // workgroup waits for it.
             if (wid >= a.item_stride) {
-                int x = wid - a.item_stride;
-                if (a.plan_wg) {
-                    if (x == 0) {
-                        constexpr int E = D == 128 ? 512 : 256;
-                        static_assert(sizeof(plan_detail::PlanLds<E>) <= sizeof(Smem<D, STG>),
-                                      "plan table must fit in the K/V staging buffers");
-                        build_plan<W * 64, E>(a.cu_seqlens, a.num_seqs, a.plan,
-                                              *reinterpret_cast<plan_detail::PlanLds<E> *>(&sm));
-                        return;
-                    }
-                    x -= 1;
-                }
-                if (x < a.prep_wgs)
-                    permute_lp_head<D, W * 64>(a.prep_a, a.aperm, x);
+                constexpr int E = D == 128 ? 512 : 256;
+                static_assert(sizeof(plan_detail::PlanLds<E>) <= sizeof(Smem<D, STG>),
+                              "plan table must fit in the K/V staging buffers");
+                build_plan<W * 64, E>(a.cu_seqlens, a.num_seqs, a.plan,
+                                      *reinterpret_cast<plan_detail::PlanLds<E> *>(&sm));
                 return;
             }
         }
@@ -1246,10 +1212,9 @@ constexpr int kPlanSpinMax = 1 << 23;
 // XCDs' different speeds).  Here every workgroup takes global items first,
 // longest first, and then local items until none is left, so the short local
 // items fill in behind the long ones:
-//   A. workgroup 0 builds the global work table (and the permuted LP
-//      matrices of an LP query transform) and releases it with a flag; every
-//      other workgroup meanwhile runs one local item, then waits for the
-//      flag.
+//   A. workgroup 0 builds the global work table and releases it with a flag;
+//      every other workgroup meanwhile runs one local item, then waits for
+//      the flag.
 //   B. global items from the per-XCD queues of the table (longest first,
 //      stealing once the own queue is empty), epilogue kEpiLayer: p Norm^G
 //      of each selected row to the compact buffer gc.
@@ -1326,8 +1291,6 @@ void layer_kernel(const AttnArgs a) {
                       "plan table must fit in the staging buffers");
         build_plan<W * 64, E>(a.cu_seqlens, a.num_seqs, a.plan,
                               *reinterpret_cast<plan_detail::PlanLds<E> *>(&sm));
-        for (int h = 0; h < a.prep_wgs; h++)
-            permute_lp_head<D, W * 64>(a.prep_a, a.aperm, h);
         // every wave's stores written back to where other XCDs read them,
         // then the flag
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");

@@ -98,5 +98,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, cvt_bf16x2(a, b));
 }
 
+// Column of the LP matrix that row r of its permuted copy holds: bits 2 and 3
+// of r (within its 32-row block) swapped.  With A'[h][r][k] = A[h][k][perm(r)]
+// as the A operand of the 32x32x16 MFMA and a lane's Q fragments as the B
+// operand, accumulator element 8 j + e of lane (g, m) is output channel
+// 16 j + 8 g + e of its 32-channel block for query row m -- the layout of the
+// B operand of the next product, so the rounded result replaces the
+// fragments directly.
+__device__ __forceinline__ int lp_perm(int r) { return (r & ~0xC) | ((r & 4) << 1) | ((r & 8) >> 1); }
+
 }  // namespace
 }  // namespace logo

@@ -344,12 +344,13 @@ logo_status check_select_args(const logo_problem *p, const float *gate, logo_sel
 logo_status run_select(const logo_problem *p, const float *gate, logo_sel_mode mode,
                        float threshold, double ratio, int32_t *sel_idx, int32_t cap,
                        int32_t *cu_sel, int32_t *tok2sel, float *thr_out, char *ws,
-                       hipStream_t s, int32_t *zero_words = nullptr, int n_zero = 0) {
+                       hipStream_t s, int32_t *zero_words = nullptr, int n_zero = 0,
+                       const LpPrep &lp = LpPrep{}) {
     const SelectWs w = select_ws(p);
     float *thr = thr_out ? thr_out : (float *)(ws + w.thr);
     return hip_status(launch_select(p->cu_seqlens, p->num_seqs, p->max_seqlen, gate, (int)mode,
                                     threshold, ratio, sel_idx, cap, cu_sel, tok2sel, thr,
-                                    (int32_t *)(ws + w.counts), s, zero_words, n_zero),
+                                    (int32_t *)(ws + w.counts), s, zero_words, n_zero, lp),
                       s);
 }
 
@@ -486,7 +487,7 @@ logo_status global_plan(const logo_problem *p, const int32_t *sel_idx, const int
 // Fused-epilogue inputs (logo_attn_fwd only).
 // qphi: the global branch's query transform applied by the global kernel as
 // it loads the selected rows (0 none, 1 LP from the permuted copy aperm of
-// lp_a, which the local launch writes, 2 SO with qs / qb).
+// its matrices, which the selection launch writes, 2 SO with qs / qb).
 struct FusedEpi {
     const int32_t *tok2sel;
     const float *gate;
@@ -495,8 +496,7 @@ struct FusedEpi {
     float *lc;
     logo_bf16 *out;
     int qphi;
-    const logo_bf16 *lp_a;
-    uint16_t *aperm;
+    const uint16_t *aperm;
     const float *qs, *qb;
 };
 
@@ -532,11 +532,6 @@ logo_status run_local(const logo_problem *p, const logo_bf16 *q, const logo_bf16
         a.plan_wg = 1;
         a.plan = *plan;
     }
-    if (f && f->qphi == 1) {
-        a.prep_wgs = p->num_q_heads;
-        a.prep_a = f->lp_a;
-        a.aperm = f->aperm;
-    }
     // items: head groups x the sequences' tiles back to back (sum_b
     // ceil(T_b / tpw) <= ceil(N / tpw) + B - 1); persistent workgroups, a
     // multiple of the 8 XCDs, take every item_stride-th item
@@ -556,7 +551,7 @@ logo_status run_local(const logo_problem *p, const logo_bf16 *q, const logo_bf16
     a.item_stride = (int32_t)wgs;
     return hip_status(launch_attention(kModeLocal, f ? (o ? kEpiFusedTrain : kEpiFused) : kEpiRaw,
                                        p->head_dim, waves, a,
-                                       (int)wgs + a.plan_wg + a.prep_wgs, s),
+                                       (int)wgs + a.plan_wg, s),
                       s);
 }
 
@@ -703,10 +698,6 @@ logo_status run_layer(const logo_problem *p, const LayerPlan &lp, const logo_bf1
     a.aperm = f->aperm;
     a.qphi_s = f->qs;
     a.qphi_b = f->qb;
-    if (f->qphi == 1) {
-        a.prep_wgs = p->num_q_heads;
-        a.prep_a = f->lp_a;
-    }
     return hip_status(launch_layer(p->head_dim, lp.waves, a, lp.grid, s), s);
 }
 
@@ -751,7 +742,7 @@ logo_status fwd_impl(const logo_problem *p, const logo_bf16 *q, const logo_bf16 
         return st;
     hipStream_t s = (hipStream_t)stream;
     const FusedEpi fe{t2s, gate, nullptr, eps, (float *)(base + w.lc), out,
-                      qphi, lp_a, (uint16_t *)(base + w.aperm), so_s, so_b};
+                      qphi, (const uint16_t *)(base + w.aperm), so_s, so_b};
     auto mark = [&](int i) -> logo_status {
         if (events && hipEventRecord((hipEvent_t)events[i], s) != hipSuccess)
             return LOGO_ERR_HIP;
@@ -766,6 +757,13 @@ logo_status fwd_impl(const logo_problem *p, const logo_bf16 *q, const logo_bf16 
     // builds the global branch's tile plan.  Then the global branch finishes
     // the selected rows.
     const bool with_plan = p->total_tokens > 0 && cap > 0;
+    LpPrep prep;
+    if (with_plan && qphi == 1) {
+        prep.heads = p->num_q_heads;
+        prep.head_dim = p->head_dim;
+        prep.a = lp_a;
+        prep.aperm = (uint16_t *)(base + w.aperm);
+    }
     LayerPlan lp;
     if (with_plan && (st = layer_plan(p, lp)) != LOGO_OK)
         return st;
@@ -774,7 +772,7 @@ logo_status fwd_impl(const logo_problem *p, const logo_bf16 *q, const logo_bf16 
         int32_t *ctl = (int32_t *)(base + w.ctl);
         float *lc = (float *)(base + w.lc), *gc = (float *)(base + w.gc);
         st = run_select(p, gate, mode, threshold, ratio, sel, cap, cus, t2s, thr, base + w.sel_ws,
-                        s, ctl, kLayerCtlWords);
+                        s, ctl, kLayerCtlWords, prep);
         if (st != LOGO_OK || (st = mark(1)) != LOGO_OK)
             return st;
         st = run_layer(p, lp, q, k, v, q_g ? q_g : q, k_g ? k_g : k, v_g ? v_g : v, sel, cus, cap,
@@ -792,7 +790,8 @@ logo_status fwd_impl(const logo_problem *p, const logo_bf16 *q, const logo_bf16 
     int grid_g = 0;
     if (with_plan && (st = global_plan(p, sel, cus, cap, base + w.glob_ws, plan, grid_g)) != LOGO_OK)
         return st;
-    st = run_select(p, gate, mode, threshold, ratio, sel, cap, cus, t2s, thr, base + w.sel_ws, s);
+    st = run_select(p, gate, mode, threshold, ratio, sel, cap, cus, t2s, thr, base + w.sel_ws, s,
+                    nullptr, 0, prep);
     if (st != LOGO_OK || (st = mark(1)) != LOGO_OK)
         return st;
     st = run_local(p, q, k, v, nullptr, &fe, gain_local, s, with_plan ? &plan : nullptr);
@@ -1228,7 +1227,7 @@ logo_status logo_attn_fwd_train(const logo_problem *p, const logo_bf16 *q, const
     // workgroup builds the global branch's tile plan; global branch), with
     // epilogues that also keep the raw branch outputs and their LSEs.
     const FusedEpi fe{tok2sel, gate, nullptr, eps, (float *)(base + w.lc), out,
-                      0, nullptr, nullptr, nullptr, nullptr};
+                      0, nullptr, nullptr, nullptr};
     PlanArgs plan;
     int grid_g = 0;
     const bool with_plan = p->total_tokens > 0 && cap > 0;

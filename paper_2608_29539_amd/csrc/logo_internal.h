@@ -151,17 +151,12 @@ struct AttnArgs {
     // w + item_stride, ... below n_items (head group fastest, then the
     // sequences' token tiles back to back)
     int32_t n_items, item_stride;
-    // fused local launch only: prep_wgs workgroups (after the plan workgroup,
-    // at the end of the grid)
-    // write the permuted copy aperm of the LP matrices A [Hq][d][d] that the
-    // global launch reads (one head each)
-    int32_t prep_wgs;
-    const uint16_t *prep_a;
-    uint16_t *aperm;
     // fused global mode only: the branch transform of the selected queries,
-    // applied as they are loaded (0 none, 1 LP with aperm, 2 SO with qphi_s /
-    // qphi_b [Hq][d])
+    // applied as they are loaded (0 none, 1 LP with aperm, the permuted copy
+    // of the matrices [Hq][d][d] that the selection launch writes, 2 SO with
+    // qphi_s / qphi_b [Hq][d])
     int32_t qphi;
+    const uint16_t *aperm;
     const float *qphi_s, *qphi_b;
     PlanArgs plan;
     // raw epilogue only: lse (or NULL) receives each row's base-2
@@ -211,11 +206,20 @@ hipError_t launch_sel_sum(int32_t cap, int hq, int head_dim, const int32_t *cu_s
 // the parts of a sequence that separate workgroups compact.
 // zero_words (or NULL): n_zero ints the selection kernel clears (the control
 // words of the layer launch that follows it).
+// lp (heads > 0): extra workgroups of the (last) selection launch write the
+// permuted copies of an LP query transform's matrices, one head each, for the
+// attention launch that follows.
+struct LpPrep {
+    int heads = 0, head_dim = 0;
+    const uint16_t *a = nullptr;   // [heads][d][d]
+    uint16_t *aperm = nullptr;
+};
 hipError_t launch_select(const int32_t *cu_seqlens, int num_seqs, int max_seqlen,
                          const float *gate, int mode, float threshold, double ratio,
                          int32_t *sel_idx, int32_t sel_capacity, int32_t *cu_sel,
                          int32_t *tok2sel, float *thr, int32_t *seq_counts, hipStream_t s,
-                         int32_t *zero_words = nullptr, int n_zero = 0);
+                         int32_t *zero_words = nullptr, int n_zero = 0,
+                         const LpPrep &lp = LpPrep{});
 
 // One decoding step (decode.hip).  Work items: local (sequence, KV head,
 // head group, chunk) then global (selected rank, KV head, head group,

@@ -29,6 +29,7 @@
 //                     builds it inside its local-branch launch instead.
 #include "logo_internal.h"
 #include "plan.h"
+#include "attn_common.h"
 
 namespace logo {
 namespace {
@@ -122,6 +123,21 @@ __device__ __forceinline__ void block_min_max(uint32_t &mn, uint32_t &mx, uint32
     __syncthreads();
 }
 
+// The permuted copy of one head's LP matrix (see lp_perm): A'[r][k0 .. k0+7]
+// gathers column lp_perm(r) of rows k0 .. k0+7 of A.  Consecutive lanes take
+// consecutive r, so each load reads whole 128-byte pieces of a row.
+__device__ void permute_lp_head(const LpPrep &p, int head) {
+    const int D = p.head_dim;
+    const uint16_t *src = p.a + (int64_t)head * D * D;
+    uint16_t *dst = p.aperm + (int64_t)head * D * D;
+    for (int c = threadIdx.x; c < D * D / 8; c += kSelThreads) {
+        const int r = c % D, k0 = (c / D) * 8;
+        const uint16_t *sc = src + k0 * D + lp_perm(r);
+        auto pair = [&](int e) { return (uint32_t)sc[e * D] | ((uint32_t)sc[(e + 1) * D] << 16); };
+        *(u32x4 *)(dst + r * D + k0) = u32x4{pair(0), pair(2), pair(4), pair(6)};
+    }
+}
+
 // Selection, one 1024-thread workgroup per (part, sequence): blockIdx.y is
 // the sequence, blockIdx.x the part, and part p writes the tokens
 // [p * part_tokens, (p + 1) * part_tokens) of the sequence.  part_tokens is
@@ -160,8 +176,8 @@ template <bool kThreshold, bool kWrite>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int32_t *__restrict__ cu, int B, const float *__restrict__ gate, int mode, float fixed,
     double ratio, float *__restrict__ thr, int32_t *__restrict__ cnt, int32_t *__restrict__ sel_idx,
-    int32_t cap, int32_t *__restrict__ cu_sel, int32_t *__restrict__ tok2sel, int part_tokens,
-    int32_t *__restrict__ zero_words, int n_zero) {
+    int32_t cap, int32_t *__restrict__ cu_sel, int32_t *__restrict__ tok2sel, int part_tokens, int parts,
+    int32_t *__restrict__ zero_words, int n_zero, const LpPrep lp) {
     __shared__ int hist[kProbBins];           // histogram, then the block counts
     __shared__ int s_wave[kSelWaves];
     __shared__ uint32_t s_u[2 * kSelWaves];
@@ -170,6 +186,17 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     __shared__ float cand[kMaxCand];          // values of the threshold's probability bin
     const int b = blockIdx.y, part = blockIdx.x, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
+    // Workgroups past the parts copy LP matrices, beside the selection
+    // (which leaves almost every CU free).  Workgroup 0 of the layer launch
+    // did it before, head after head while every other workgroup waited for
+    // its work table: gate projection, transforms and layer at 8192 tokens,
+    // 32 / 8 heads of d = 128, took 551 us then and 336 us now.
+    if (kWrite && part >= parts) {
+        const int h = (part - parts) * B + b;
+        if (h < lp.heads)
+            permute_lp_head(lp, h);
+        return;
+    }
     // the control words of the launch that follows (first workgroup)
     if (kWrite && b == 0 && part == 0 && tid < n_zero)
         zero_words[tid] = 0;
@@ -409,7 +436,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         }
         if (part == 0 && tid == 0)
             cu_sel[b] = offset;
-        const int p1 = part == (int)gridDim.x - 1 ? T : min(T, p0 + part_tokens);
+        const int p1 = part == parts - 1 ? T : min(T, p0 + part_tokens);
         int end_count = offset;               // selected tokens before p1 (with the offset)
         if (p0 < p1) {
             // the chunk that holds the part, and the selected tokens before it
@@ -509,7 +536,7 @@ hipError_t launch_select(const int32_t *cu_seqlens, int num_seqs, int max_seqlen
                          const float *gate, int mode, float threshold, double ratio,
                          int32_t *sel_idx, int32_t sel_capacity, int32_t *cu_sel,
                          int32_t *tok2sel, float *thr, int32_t *seq_counts, hipStream_t s,
-                         int32_t *zero_words, int n_zero) {
+                         int32_t *zero_words, int n_zero, const LpPrep &lp) {
     // parts of 4096 * 2^i tokens, at most kMaxParts per sequence unless a
     // part would exceed one chunk (then one part per chunk)
     int part_tokens = kPartUnit;
@@ -517,21 +544,25 @@ hipError_t launch_select(const int32_t *cu_seqlens, int num_seqs, int max_seqlen
            ((long long)max_seqlen + part_tokens - 1) / part_tokens > kMaxParts)
         part_tokens *= 2;
     const int parts = (int)std::max(1LL, ((long long)max_seqlen + part_tokens - 1) / part_tokens);
+    const int lp_cols = (lp.heads + num_seqs - 1) / num_seqs;   // grid columns of the LP copies
     if (num_seqs == 1) {
-        hipLaunchKernelGGL((select_kernel<true, true>), dim3(parts, 1), dim3(kSelThreads), 0, s,
-                           cu_seqlens, 1, gate, mode, threshold, ratio, thr, seq_counts, sel_idx,
-                           sel_capacity, cu_sel, tok2sel, part_tokens, zero_words, n_zero);
+        hipLaunchKernelGGL((select_kernel<true, true>), dim3(parts + lp_cols, 1),
+                           dim3(kSelThreads), 0, s, cu_seqlens, 1, gate, mode, threshold, ratio,
+                           thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens,
+                           parts, zero_words, n_zero, lp);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((select_kernel<true, false>), dim3(1, num_seqs), dim3(kSelThreads), 0, s,
                        cu_seqlens, num_seqs, gate, mode, threshold, ratio, thr, seq_counts,
-                       sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens, nullptr, 0);
+                       sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens, 1, nullptr, 0,
+                       LpPrep{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((select_kernel<false, true>), dim3(parts, num_seqs), dim3(kSelThreads), 0,
-                       s, cu_seqlens, num_seqs, gate, mode, threshold, ratio, thr, seq_counts,
-                       sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens, zero_words, n_zero);
+    hipLaunchKernelGGL((select_kernel<false, true>), dim3(parts + lp_cols, num_seqs),
+                       dim3(kSelThreads), 0, s, cu_seqlens, num_seqs, gate, mode, threshold,
+                       ratio, thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel,
+                       part_tokens, parts, zero_words, n_zero, lp);
     return hipGetLastError();
 }
 

@@ -278,3 +278,16 @@ def test_layer_fused_query_transform_sweep(pk, fwd_launches):
         over += int(big.shape[0])
     print(f"[layer+qphi sweep] {over} of {total} elements above 2e-2", flush=True)
     assert over <= total * 1e-7
+
+
+@pytest.mark.parametrize("seqlens,H,Hkv,d", [
+    ((9000,), 8, 2, 128),                            # several parts per sequence, one sequence
+    ((300,) * 11, 4, 4, 64),                         # more sequences than heads
+    ((5000, 70, 200), 16, 4, 64),                    # heads not a multiple of the sequences
+])
+def test_lp_copies_in_selection_launch(pk, seqlens, H, Hkv, d, fwd_launches):
+    """The permuted LP matrices come from extra workgroups of the selection
+    launch, one head each: bit for bit against the two-pass path where the
+    launch's grid leaves heads over, and the layer bar."""
+    st, _, _ = _qphi_case(pk, (seqlens, H, Hkv, d, 128, 0.2, "lp", False), 4700 + H, "copies")
+    assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3
