@@ -21,6 +21,11 @@ ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# Per source.  bwd.hip: MFMA accumulators in VGPRs where the vector ALU reads
+# them (the scores); the default at more than 256 registers puts all of them in
+# AGPRs, one copy per value and use.
+EXTRA = {"bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
 
 def hipcc() -> str:
     path = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -35,7 +40,7 @@ def sources():
 
 
 def _compile(src: str, obj: str) -> None:
-    cmd = [hipcc(), *COMMON, "-x", "hip", "-c", src, "-o", obj]
+    cmd = [hipcc(), *COMMON, *EXTRA.get(os.path.basename(src), []), "-x", "hip", "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:

@@ -54,15 +54,36 @@ __device__ __forceinline__ u32x4 raw_rsrc(const void *p, int nbytes) {
 // the compiler does not make every later LDS read wait for it: the buffer it
 // fills is only read after the wait + barrier that ends the pipeline step.
 // M0 (the LDS base of the load) is saved and restored around it.
-__device__ __forceinline__ void lds_load16(u32x4 r, const void *lds, int voffset) {
-    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds);
+__device__ __forceinline__ void lds_load16_at(u32x4 r, uint32_t lds, int voffset) {
+    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(lds);
     uint32_t saved;
     asm volatile(
         "s_mov_b32 %0, m0\n\t"
         "s_mov_b32 m0, %1\n\t"
         "s_nop 0\n\t"
         "buffer_load_dwordx4 %2, %3, 0 offen lds\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(lds_addr), "v"(voffset), "s"(r)
+        : "memory");
+}
+// LDS address (byte offset in the workgroup's LDS) of a shared object.
+__device__ __forceinline__ uint32_t lds_addr_of(const void *lds) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds;
+}
+__device__ __forceinline__ void lds_load16(u32x4 r, const void *lds, int voffset) {
+    lds_load16_at(r, lds_addr_of(lds), voffset);
+}
+
+// The same with 4 bytes per lane (lane i writes the 4 bytes at lds + 4 i).
+__device__ __forceinline__ void lds_load4_at(u32x4 r, uint32_t lds, int voffset) {
+    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(lds);
+    uint32_t saved;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %1\n\t"
+        "s_nop 0\n\t"
+        "buffer_load_dword %2, %3, 0 offen lds\n\t"
         "s_mov_b32 m0, %0"
         : "=&s"(saved)
         : "s"(lds_addr), "v"(voffset), "s"(r)
@@ -88,6 +109,19 @@ __device__ __forceinline__ bf16x8 lds_tr_pair(const void *a0, const void *a1) {
     const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a1);
     const s16x4 ab[2] = {a, b};
     return __builtin_bit_cast(bf16x8, ab);
+}
+
+// The same where the kPending newest of this wave's LDS-bound loads may still
+// be in flight (kPending < 16): a bare barrier, whose memory fence would wait
+// for them.  Every LDS read before it has returned its data already (the
+// caller's products took it), and the compiler may not move accesses across.
+template <int kPending>
+__device__ __forceinline__ void dma_wait_barrier_but() {
+    static_assert(kPending >= 0 && kPending < 16, "vmcnt field");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | kPending);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // Two fp32 -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32.

@@ -38,9 +38,21 @@
 #include "attn_common.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace logo {
 namespace {
+
+// f(integral_constant 0) ... f(integral_constant N - 1): unrolled by
+// construction, so that every index is a compile-time constant.
+template <int... I, class F>
+__device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(std::make_integer_sequence<int, N>{}, f);
+}
 
 constexpr int kBwdWaves = 4;
 constexpr int kTileRows = 64;   // rows of a staged tile (keys or queries)
@@ -74,11 +86,18 @@ __device__ __forceinline__ void tile_dma_plan(TileDma<D> &d, int wave, int lane,
         d.voff[i] = row * row_bytes + ((p ^ swz<D>(row)) << 4);
     }
 }
+// dst: the LDS address of the tile (lds_addr_of)
+// (tile_dma_part: the i-th of the wave's loads)
 template <int D>
-__device__ __forceinline__ void tile_dma(void *dst, const TileDma<D> &d, u32x4 r, int wave) {
+__device__ __forceinline__ void tile_dma_part(uint32_t dst, const TileDma<D> &d, u32x4 r, int wave,
+                                              int i) {
+    lds_load16_at(r, dst + (i * kBwdWaves + wave) * 1024, d.voff[i]);
+}
+template <int D>
+__device__ __forceinline__ void tile_dma(uint32_t dst, const TileDma<D> &d, u32x4 r, int wave) {
 #pragma unroll
     for (int i = 0; i < TileDma<D>::kPerWave; i++)
-        lds_load16(r, (char *)dst + (i * kBwdWaves + wave) * 1024, d.voff[i]);
+        lds_load16_at(r, dst + (i * kBwdWaves + wave) * 1024, d.voff[i]);
 }
 
 // Per-lane LDS offsets of the two fragment kinds inside a tile:
@@ -131,11 +150,17 @@ __device__ __forceinline__ bf16x8 pack8(const bf16x2 (&w)[8], int half) {
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
+// Two waves per SIMD, bound by MFMA issue and, over long runs, by the power
+// budget (1.7 GHz at 64% of the matrix cycles).  Dense causal, 8192 tokens,
+// 32 / 8 heads, d = 128: 690 us (1195 TFLOP/s executed), against 731 us with
+// each half's softmax between its own products, 4 spilled registers and a
+// branch per tile; 4096 selected rows of 32768 tokens: 1460 against 1629 us.
 template <int D, int MODE>
 __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_dq_kernel(const BwdArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t sk[2][kTileRows * D];
-    __shared__ __attribute__((aligned(16))) uint16_t sv[2][kTileRows * D];
+    constexpr int kTileBytes = kTileRows * D * 2;
+    // two buffers of (K tile, V tile)
+    __shared__ __attribute__((aligned(16))) char stile[2][2][kTileBytes];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uni(tid >> 6);
     const int g = lane >> 5, m = lane & 31;
@@ -178,7 +203,7 @@ void bwd_dq_kernel(const BwdArgs a) {
         }
     }
     const float lse = a.lse[(int64_t)head * a.row_stride + r];
-    const float dlt = a.delta[(int64_t)head * a.row_stride + r];
+    const float ndlt = a.ndelta[(int64_t)head * a.row_stride + r];
     const float c = a.scale_log2;
 
     const int w = a.window;
@@ -205,11 +230,12 @@ void bwd_dq_kernel(const BwdArgs a) {
     tile_dma_plan<D>(dma, wave, lane, row_bytes);
     FragOffsets<D> fo;
     frag_offsets<D>(fo, lane);
-    auto stage = [&](int kb_, int buf) {
+    auto stage = [&](int kb_, int buf) __attribute__((always_inline)) {
         const int k0 = kb_ * kTileRows;
         const int nb = max(0, min(kTileRows, T - k0)) * row_bytes;
-        tile_dma<D>(sk[buf], dma, raw_rsrc(kbase + (int64_t)k0 * a.hkv * D, nb), wave);
-        tile_dma<D>(sv[buf], dma, raw_rsrc(vbase + (int64_t)k0 * a.hkv * D, nb), wave);
+        const uint32_t dst = lds_addr_of(&stile[0][0][0]) + buf * 2 * kTileBytes;
+        tile_dma<D>(dst, dma, raw_rsrc(kbase + (int64_t)k0 * a.hkv * D, nb), wave);
+        tile_dma<D>(dst + kTileBytes, dma, raw_rsrc(vbase + (int64_t)k0 * a.hkv * D, nb), wave);
     };
 
     f32x16 acc[D / 32];
@@ -217,95 +243,129 @@ void bwd_dq_kernel(const BwdArgs a) {
     for (int cb = 0; cb < D / 32; cb++)
         acc[cb] = f32x16{};
 
-    // bufc: the buffer as a compile-time constant, so that every fragment
-    // address is a per-lane offset plus an immediate.  masked: a compile-time
-    // flag (a runtime one is if-converted into selects on every tile).
-    auto compute = [&](int kb_, auto bufc, auto masked) {
-        constexpr int B = decltype(bufc)::value;
-        const char *kt = (const char *)sk[B];
-        const char *vt = (const char *)sv[B];
+    // One 64-key tile: 3 D / 8 MFMAs in four blocks, the two 32-key halves
+    // skewed so that each half's softmax has independent MFMAs beside it:
+    //   S, dP (half 0) | S, dP (half 1) + softmax (half 0) |
+    //   dQ (half 0) + softmax (half 1) | dQ (half 1)
+    // Chunk n holds the LDS reads of MFMA n + kAhead's operand, MFMA n and a
+    // slice of a softmax; the scheduler may not move anything between chunks.
+    constexpr int NM = D / 8;                // MFMAs of a block of S and dP
+    constexpr int kAhead = 3;                // operand fragments in flight
+    auto compute = [&](int kb_, auto masked) __attribute__((always_inline)) {
         const int k0 = kb_ * kTileRows;
-#pragma unroll
-        for (int sb = 0; sb < 2; sb++) {
-            f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-            for (int ss = 0; ss < D / 16; ss++) {
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_at(kt + sb * 32 * D * 2, fo.row[ss]), qf[ss], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_at(vt + sb * 32 * D * 2, fo.row[ss]), dof[ss], dp, 0, 0, 0);
+        f32x16 s[2], dp[2];
+        float p[2][2];
+        bf16x2 dsw[2][8];
+        bf16x8 fr[kAhead + 1];
+        // MFMA n: its LDS operand, and the product
+        auto load = [&](int n) __attribute__((always_inline)) {
+            if (n < 2 * NM) {
+                const int sb = n / NM, i = n % NM;
+                return frag_at(stile[0][i & 1] + sb * 32 * D * 2, fo.row[i / 2]);
             }
-            // Schedule: two fragment reads ahead, then one MFMA per read, so
-            // only a few fragments are live at a time (the register budget
-            // of two waves per SIMD).
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);       // DS read
-#pragma unroll
-            for (int i = 0; i < D / 8 - 2; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            const int i = n - 2 * NM, sb = i / (NM / 2), j = i % (NM / 2);
+            return frag_tr<D>(stile[0][0], fo, sb * 32 + (j / (NM / 4)) * 16, j % (NM / 4));
+        };
+        auto mfma = [&](int n) __attribute__((always_inline)) {
+            const bf16x8 f = fr[n % (kAhead + 1)];
+            if (n < 2 * NM) {
+                const int sb = n / NM, i = n % NM;
+                if (i % 2 == 0)
+                    s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[i / 2], s[sb], 0, 0, 0);
+                else
+                    dp[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[i / 2], dp[sb], 0, 0, 0);
+            } else {
+                const int i = n - 2 * NM, sb = i / (NM / 2), j = i % (NM / 2), cb = j % (NM / 4);
+                acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pack8(dsw[sb], j / (NM / 4)),
+                                                                  acc[cb], 0, 0, 0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            // lane: query column; register i: key k0 + 32 sb + 8 (i/4) + 4 g + i%4
-            bf16x2 dsw[8];
+        };
+        // softmax backward of half sb, element pair j: P = 2^(c S - lse),
+        // then dS = P (dP - Delta) rounded to bf16.  Lane: query column;
+        // element i: key k0 + 32 sb + 8 (i/4) + 4 g + i%4.
+        auto soft_p = [&](int sb, int j) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                float d2[2];
-#pragma unroll
-                for (int e = 0; e < 2; e++) {
-                    float p = __builtin_amdgcn_exp2f(fmaf(s[i + e], c, -lse));
-                    if constexpr (decltype(masked)::value) {
-                        const int key = k0 + sb * 32 + ((i + e) >> 2) * 8 + g * 4 + ((i + e) & 3);
-                        bool ok = key <= pos;
-                        if (MODE == kModeLocal)
-                            ok = ok && key > pos - w;
-                        p = ok ? p : 0.f;
-                    }
-                    d2[e] = p * (dp[i + e] - dlt);
+            for (int e = 0; e < 2; e++) {
+                const int i = 2 * j + e;
+                float x = fmaf(s[sb][i], c, -lse);
+                if constexpr (decltype(masked)::value) {
+                    const int key = k0 + sb * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
+                    bool ok = key <= pos;
+                    if (MODE == kModeLocal)
+                        ok = ok & (key > pos - w);
+                    x = ok ? x : kNegInf;                // P = 0
                 }
-                dsw[i >> 1] = cvt_bf16x2(d2[0], d2[1]);
+                p[sb][e] = __builtin_amdgcn_exp2f(x);
             }
+        };
+        auto soft_ds = [&](int sb, int j) __attribute__((always_inline)) {
+            dsw[sb][j] = cvt_bf16x2(p[sb][0] * (dp[sb][2 * j] + ndlt), p[sb][1] * (dp[sb][2 * j + 1] + ndlt));
+        };
+        s[0] = s[1] = dp[0] = dp[1] = f32x16{};
 #pragma unroll
-            for (int half = 0; half < 2; half++) {
-                const bf16x8 bf = pack8(dsw, half);
-#pragma unroll
-                for (int cb = 0; cb < D / 32; cb++)
-                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        frag_tr<D>(kt, fo, sb * 32 + half * 16, cb), bf, acc[cb], 0, 0, 0);
-            }
-            // one transposed fragment (two reads) ahead of each MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-            for (int i = 0; i < D / 16 - 1; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
+        for (int n = 0; n < kAhead; n++)
+            fr[n] = load(n);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<3 * NM>([&](auto nc) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            if constexpr (n + kAhead < 3 * NM)
+                fr[(n + kAhead) % (kAhead + 1)] = load(n + kAhead);
+            mfma(n);
+            // half 0: one pair every NM / 8 chunks; half 1: twice as dense
+            static_for<8>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                constexpr int a0 = NM + 1 + j * (NM / 8), a1 = 2 * NM + 1 + j * NM / 16;
+                if constexpr (n == a0 + 1)
+                    soft_ds(0, j);
+                if constexpr (n == a0)
+                    soft_p(0, j);
+                if constexpr (NM == 8 && n == a1) {
+                    soft_p(1, j);
+                    soft_ds(1, j);
+                }
+                if constexpr (NM != 8 && n == a1 + 1)
+                    soft_ds(1, j);
+                if constexpr (NM != 8 && n == a1)
+                    soft_p(1, j);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
 
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
+    using T_ = std::true_type;
+    using F_ = std::false_type;
     // Step kb (buffer (kb - kb_lo) % 2): stage tile kb+1 into the other
-    // buffer, compute tile kb, then wait for the staged loads and barrier.
-    auto step = [&](int kb_, auto bufc) {
-        constexpr int B = decltype(bufc)::value;
+    // buffer, run `work` on tile kb, then wait for the staged loads and
+    // barrier.  The fragment offsets point into the current buffer.
+    auto step = [&](int kb_, auto &&work) __attribute__((always_inline)) {
         if (kb_ < kb_hi)
-            stage(kb_ + 1, B ^ 1);
-        if (kb_ >= kb_first && kb_ <= kb_last) {
-            if (kb_ > kb_c || kb_ < kb_w)
-                compute(kb_, bufc, std::true_type{});
-            else
-                compute(kb_, bufc, std::false_type{});
-        }
+            stage(kb_ + 1, ((kb_ - kb_lo) & 1) ^ 1);
+        work();
         dma_wait_barrier();
+#pragma unroll
+        for (int i = 0; i < D / 16; i++)
+            fo.row[i] ^= 2 * kTileBytes;
+#pragma unroll
+        for (int i = 0; i < D / 32; i++) {
+            fo.tr0[i] ^= 2 * kTileBytes;
+            fo.tr1[i] ^= 2 * kTileBytes;
+        }
     };
     stage(kb_lo, 0);
     dma_wait_barrier();
-    for (int kb = kb_lo; kb <= kb_hi; kb += 2) {
-        step(kb, I0{});
-        if (kb + 1 <= kb_hi)
-            step(kb + 1, I1{});
-    }
+    // Loops of a single kind each: tiles only the other waves see, window
+    // edge, unmasked, diagonal.
+    int kb = kb_lo;
+    for (; kb < kb_first && kb <= kb_hi; kb++)
+        step(kb, [] {});
+    for (; kb <= kb_last && kb < kb_w; kb++)
+        step(kb, [&]() __attribute__((always_inline)) { compute(kb, T_{}); });
+    for (; kb <= kb_last && kb <= kb_c; kb++)
+        step(kb, [&]() __attribute__((always_inline)) { compute(kb, F_{}); });
+    for (; kb <= kb_last; kb++)
+        step(kb, [&]() __attribute__((always_inline)) { compute(kb, T_{}); });
+    for (; kb <= kb_hi; kb++)
+        step(kb, [] {});
 
     if (!(wave_valid && valid))
         return;
@@ -327,17 +387,27 @@ void bwd_dq_kernel(const BwdArgs a) {
 // ---------------------------------------------------------------------------
 // dK, dV
 // ---------------------------------------------------------------------------
+// One wave per SIMD (32 keys: K and V fragments in AGPRs, dK and dV in the
+// accumulators, both halves' scores in VGPRs).  What bounds it, by leaving
+// parts out (dense causal, 8192 tokens, 32 / 8 heads, d = 128, 960 us): the
+// MFMAs and the softmax 680 us, the LDS reads of one fragment per MFMA
+// another 200 (each costs the wave ~6 cycles of issue, however far ahead it
+// is made), the tile loads 80-100.  It took 1140 us with each half's softmax
+// between its own products, the score accumulators in AGPRs (a copy per value
+// read) and the row scalars staged through registers; dK, dV of the selected
+// rows of 32768 tokens: 2430 -> 2080 us, of the local branch: 1300 -> 1083.
 constexpr int kKeysPerWg = kBwdWaves * 32;
 
 template <int D, int MODE>
 __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void bwd_dkv_kernel(const BwdArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t sq[2][kTileRows * D];
-    __shared__ __attribute__((aligned(16))) uint16_t sd[2][kTileRows * D];
-    // per-row lse, Delta and (global) token index of the staged tiles
-    __shared__ __attribute__((aligned(16))) float sl[2][kTileRows];
-    __shared__ __attribute__((aligned(16))) float sdl[2][kTileRows];
-    __shared__ __attribute__((aligned(16))) int32_t sp[2][kTileRows];
+    constexpr int kTileBytes = kTileRows * D * 2;
+    constexpr int kBufs = 3;
+    // buffers of (Q tile, dO tile) and the rows' scalars: lse, -Delta, (global)
+    // token index; the fourth row is a place for a load that keeps the waves'
+    // numbers of loads equal
+    __shared__ __attribute__((aligned(16))) char stile[kBufs][2][kTileBytes];
+    __shared__ __attribute__((aligned(16))) float srow[kBufs][4][kTileRows];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uni(tid >> 6);
     const int g = lane >> 5, m = lane & 31;
@@ -365,6 +435,15 @@ void bwd_dkv_kernel(const BwdArgs a) {
         }
     }
 
+    // At d = 128 the fragments live in AGPRs, where the products read them in
+    // place: left to itself the compiler fills the VGPRs first and copies
+    // fragments back and forth in the loop.
+    if constexpr (D == 128) {
+#pragma unroll
+        for (int ss = 0; ss < D / 16; ss++)
+            asm volatile("" : "+a"(kf[ss]), "+a"(vf[ss]));
+    }
+
     // Rows that can see a key of this block: local, positions k0 .. k0+127+w-1;
     // global, the compacted rows from the first one at or after k0.
     int r_begin, r_end;
@@ -388,45 +467,72 @@ void bwd_dkv_kernel(const BwdArgs a) {
     const int nblk = (r_end - r_begin + kTileRows - 1) / kTileRows;
     const int nsteps = nblk * a.group;                       // every head of the KV group
 
+    // The 64-row tiles q of a head that this wave computes, qf .. ql, and
+    // among them the ones that need no mask, qa .. qb - 1: every row of such
+    // a tile sees all of the wave's keys.  (The same for every head; the
+    // other waves' tiles are only staged.)
+    int qf = 0, ql = nblk - 1, qa = 0, qb = (r_end - r_begin) / kTileRows;
+    auto row_pos = [&](int r) { return (MODE == kModeGlobal ? uni(a.sel_idx[r]) : r) - base; };
+    if (j0 >= T) {
+        qf = nblk;
+    } else {
+        while (qf < nblk && row_pos(min(r_begin + qf * kTileRows + kTileRows, r_end) - 1) < j0)
+            qf++;
+        qa = qf;
+        while (qa < nblk && row_pos(r_begin + qa * kTileRows) < j0 + 31)
+            qa++;
+        if (MODE == kModeLocal) {
+            const int jmax = min(j0 + 31, T - 1);
+            ql = (int)min((long long)ql, ((long long)jmax + w - 1 - k0) / kTileRows);
+            const long long full = (long long)j0 + w - k0;   // rows from k0 that see key j0
+            qb = (int)min((long long)qb, full / kTileRows);
+        }
+        if (j0 + 31 >= T)
+            qb = 0;
+        qb = max(qa, min(qb, ql + 1));
+    }
+
     const int row_bytes = a.hq * D * 2;
     TileDma<D> dma;
     tile_dma_plan<D>(dma, wave, lane, row_bytes);
     FragOffsets<D> fo;
     frag_offsets<D>(fo, lane);
-    auto step_rows = [&](int st, int &head, int &r0, int &nv) {
-        const int hh = st / nblk, qb = st % nblk;
-        head = kvh * a.group + hh;
-        r0 = r_begin + qb * kTileRows;
-        nv = min(kTileRows, r_end - r0);
+    // Staging of tile q of head hh into buffer buf, all of it global -> LDS:
+    // the Q / dO tiles, and the rows' lse (wave 0), -Delta (wave 1) and token
+    // index (wave 2).  Rows past the tile's end read as zeros, which no row
+    // uses.  (Scalars that pass through a register of the wave instead make
+    // it wait for them in the middle of the step: 1209 against 1003 us for
+    // the dense backward at 8192 tokens, 32 / 8 heads, d = 128.)
+    constexpr int kLoads = 2 * TileDma<D>::kPerWave + 1;     // of each wave
+    const uint32_t lds_tile = lds_addr_of(&stile[0][0][0]), lds_row = lds_addr_of(&srow[0][0][0]);
+    struct Stage {
+        u32x4 q, dout, row;
+        uint32_t tile, rows;
     };
-    // Staging of step st into buffer buf: the Q / dO tiles go global -> LDS
-    // directly; the per-row scalars are loaded into a register of one lane
-    // per row (wave 0: lse, 1: Delta, 2: token index) by stage() and written
-    // to LDS by commit() after the current step's compute, so their latency
-    // hides behind it.  Rows past the tile's end get values no row uses.
-    float row_val = 0.f;
-    auto stage = [&](int st, int buf) {
-        int head, r0, nv;
-        step_rows(st, head, r0, nv);
+    auto stage_of = [&](int hh, int q, int buf) __attribute__((always_inline)) {
+        const int head = kvh * a.group + hh;
+        const int r0 = r_begin + q * kTileRows, nv = min(kTileRows, r_end - r0);
         const int64_t off = ((int64_t)r0 * a.hq + head) * D;
-        tile_dma<D>(sq[buf], dma, raw_rsrc(a.q + off, nv * row_bytes), wave);
-        tile_dma<D>(sd[buf], dma, raw_rsrc(a.dout + off, nv * row_bytes), wave);
         const int64_t ro = (int64_t)head * a.row_stride + r0;
-        const int rr = min(lane, nv - 1);
-        if (wave == 0)
-            row_val = a.lse[ro + rr];
-        else if (wave == 1)
-            row_val = a.delta[ro + rr];
-        else if (wave == 2 && MODE == kModeGlobal)
-            row_val = __int_as_float(a.sel_idx[r0 + rr]);
+        const void *src = wave == 1 ? a.ndelta + ro : a.lse + ro;
+        if (MODE == kModeGlobal && wave == 2)
+            src = a.sel_idx + r0;
+        return Stage{raw_rsrc(a.q + off, nv * row_bytes), raw_rsrc(a.dout + off, nv * row_bytes),
+                     raw_rsrc(src, nv * 4), lds_tile + buf * 2 * kTileBytes,
+                     lds_row + (buf * 4 + wave) * kTileRows * 4};
     };
-    auto commit = [&](int buf) {
-        if (wave == 0)
-            sl[buf][lane] = row_val;
-        else if (wave == 1)
-            sdl[buf][lane] = row_val;
-        else if (wave == 2 && MODE == kModeGlobal)
-            sp[buf][lane] = __float_as_int(row_val);
+    // the i-th of the wave's loads
+    auto stage_part = [&](const Stage &sg, int i) __attribute__((always_inline)) {
+        constexpr int P = TileDma<D>::kPerWave;
+        if (i < P)
+            tile_dma_part<D>(sg.tile, dma, sg.q, wave, i);
+        else if (i < 2 * P)
+            tile_dma_part<D>(sg.tile + kTileBytes, dma, sg.dout, wave, i - P);
+        else
+            lds_load4_at(sg.row, sg.rows, lane * 4);
+    };
+    auto stage_all = [&](const Stage &sg) __attribute__((always_inline)) {
+        static_for<kLoads>([&](auto i) { stage_part(sg, decltype(i)::value); });
     };
 
     f32x16 dk[D / 32], dv[D / 32];
@@ -434,126 +540,172 @@ void bwd_dkv_kernel(const BwdArgs a) {
     for (int cb = 0; cb < D / 32; cb++)
         dk[cb] = dv[cb] = f32x16{};
     const float c = a.scale_log2;
-    const int jmax = min(j0 + 31, T - 1);
 
-    // One 64-row step: two halves of 32 query rows.
-    // One MFMA path for masked and unmasked tiles (two instantiations would
-    // give the loop-carried dK / dV accumulators different registers on the
-    // two paths and copies where they merge); the mask is a uniform branch
-    // in the softmax part only.
-    auto compute = [&](auto bufc, int r0, int nv, bool masked) {
-        constexpr int buf = decltype(bufc)::value;
-        const char *qt = (const char *)sq[buf];
-        const char *dt = (const char *)sd[buf];
-        // Both 32-row halves in one straight-line block (rows past nv are
-        // masked), so the scheduler can overlap one half's softmax with the
-        // other half's MFMAs.
+    // One 64-row tile: 4 D / 8 MFMAs in four blocks, the two 32-row halves
+    // skewed so that each half's softmax has independent MFMAs beside it:
+    //   S, dP (half 0) | S, dP (half 1) + softmax (half 0) |
+    //   dV, dK (half 0) + softmax (half 1) | dV, dK (half 1)
+    // One wave runs per SIMD (the accumulators and the K / V fragments take
+    // the registers of two), so the overlap has to be in the instruction
+    // order: chunk n holds the LDS reads of MFMA n + kAhead's operand, MFMA n
+    // and a slice of a softmax, and the scheduler may not move anything
+    // between chunks.
+    constexpr int NM = D / 8;                // MFMAs of a block
+    constexpr int kAhead = 3;                // operand fragments in flight
+    auto compute = [&](int buf, int q, const Stage &sg, auto masked)
+                       __attribute__((always_inline)) {
+        const char *qt = stile[buf][0], *dt = stile[buf][1];
+        const int r0 = r_begin + q * kTileRows, nv = min(kTileRows, r_end - r0);
+        f32x16 s[2], dp[2];
+        f32x4 l4[2][4];
+        float p[2][16];
+        bf16x2 pw[2][8], dsw[2][8];
+        bf16x8 fr[kAhead + 1];
+        // MFMA n: its LDS operand, and the product
+        auto load = [&](int n) __attribute__((always_inline)) {
+            const int qh = (n / NM) & 1, i = n % NM;
+            const char *t = ((n < 2 * NM) == (i % 2 == 0)) ? qt : dt;
+            if (n < 2 * NM)
+                return frag_at(t + qh * 32 * D * 2, fo.row[i / 2]);
+            return frag_tr<D>(t, fo, qh * 32 + (i / (NM / 2)) * 16, (i % (NM / 2)) / 2);
+        };
+        auto mfma = [&](int n) __attribute__((always_inline)) {
+            const int qh = (n / NM) & 1, i = n % NM;
+            const bf16x8 f = fr[n % (kAhead + 1)];
+            if (n < 2 * NM) {
+                if (i % 2 == 0)
+                    s[qh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[i / 2], s[qh], 0, 0, 0);
+                else
+                    dp[qh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, vf[i / 2], dp[qh], 0, 0, 0);
+            } else {
+                const int half = i / (NM / 2), cb = (i % (NM / 2)) / 2;
+                if (i % 2 == 0)
+                    dv[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pack8(pw[qh], half),
+                                                                     dv[cb], 0, 0, 0);
+                else
+                    dk[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pack8(dsw[qh], half),
+                                                                     dk[cb], 0, 0, 0);
+            }
+        };
+        // softmax of half qh, element pair j: P = 2^(c S - lse), then dS =
+        // P (dP - Delta) and both rounded to bf16.  Lane: key column; element
+        // i: row qh*32 + 8 (i/4) + 4 g + i%4.
+        auto soft_p = [&](int qh, int j) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const int i = 2 * j + e;
+                float x = fmaf(s[qh][i], c, -l4[qh][i / 4][i % 4]);
+                if constexpr (decltype(masked)::value) {
+                    const int qi = qh * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
+                    const int qpos = (MODE == kModeGlobal ? __float_as_int(srow[buf][2][qi]) : r0 + qi) - base;
+                    bool ok = (qi < nv) & (key <= qpos);
+                    if (MODE == kModeLocal)
+                        ok = ok & (qpos < key + w);
+                    x = ok ? x : kNegInf;                // P = 0
+                }
+                p[qh][i] = __builtin_amdgcn_exp2f(x);
+            }
+        };
+        auto soft_ds = [&](int qh, int j) __attribute__((always_inline)) {
+            pw[qh][j] = cvt_bf16x2(p[qh][2 * j], p[qh][2 * j + 1]);
+            dsw[qh][j] = cvt_bf16x2(p[qh][2 * j] * dp[qh][2 * j], p[qh][2 * j + 1] * dp[qh][2 * j + 1]);
+        };
+        // S starts from zero, dP from -Delta
 #pragma unroll
         for (int qh = 0; qh < 2; qh++) {
-            f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-            for (int ss = 0; ss < D / 16; ss++) {
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_at(qt + qh * 32 * D * 2, fo.row[ss]), kf[ss], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    frag_at(dt + qh * 32 * D * 2, fo.row[ss]), vf[ss], dp, 0, 0, 0);
-            }
-            // six fragment reads ahead, then one MFMA per read
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-#pragma unroll
-            for (int i = 0; i < D / 8 - 6; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-            // lane: key column; register i: row qh*32 + 8 (i/4) + 4 g + i%4
-            float p[16], dl[16];
+            s[qh] = f32x16{};
 #pragma unroll
             for (int qd = 0; qd < 4; qd++) {
-                const int ro = qh * 32 + qd * 8 + g * 4;
-                const f32x4 l4 = *(const f32x4 *)&sl[buf][ro];
-                const f32x4 d4 = *(const f32x4 *)&sdl[buf][ro];
+                const f32x4 d4 = *(const f32x4 *)&srow[buf][1][qh * 32 + qd * 8 + g * 4];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    p[qd * 4 + e] = __builtin_amdgcn_exp2f(fmaf(s[qd * 4 + e], c, -l4[e]));
-                    dl[qd * 4 + e] = d4[e];
-                }
+                for (int e = 0; e < 4; e++)
+                    dp[qh][qd * 4 + e] = d4[e];
             }
-            if (masked) {
-#pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const int qi = qh * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
-                    const int qpos = (MODE == kModeGlobal ? sp[buf][qi] : r0 + qi) - base;
-                    bool ok = qi < nv && key <= qpos;
-                    if (MODE == kModeLocal)
-                        ok = ok && qpos < key + w;
-                    p[i] = ok ? p[i] : 0.f;
-                }
-            }
-            bf16x2 pw[8], dsw[8];
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                pw[i >> 1] = cvt_bf16x2(p[i], p[i + 1]);
-                dsw[i >> 1] = cvt_bf16x2(p[i] * (dp[i] - dl[i]), p[i + 1] * (dp[i + 1] - dl[i + 1]));
-            }
-#pragma unroll
-            for (int half = 0; half < 2; half++) {
-                const bf16x8 pb = pack8(pw, half), db = pack8(dsw, half);
-#pragma unroll
-                for (int cb = 0; cb < D / 32; cb++) {
-                    dv[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        frag_tr<D>(dt, fo, qh * 32 + half * 16, cb), pb, dv[cb], 0, 0, 0);
-                    dk[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        frag_tr<D>(qt, fo, qh * 32 + half * 16, cb), db, dk[cb], 0, 0, 0);
-                }
-            }
-            // two transposed fragments (four reads) ahead of the MFMAs
-            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-            for (int i = 0; i < D / 8 - 4; i++) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
         }
+#pragma unroll
+        for (int n = 0; n < kAhead; n++)
+            fr[n] = load(n);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<4 * NM>([&](auto nc) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            if constexpr (n + kAhead < 4 * NM)
+                fr[(n + kAhead) % (kAhead + 1)] = load(n + kAhead);
+            // lse of each half's rows, four reads before its softmax
+            constexpr int l0 = n - (NM - 4), l1 = n - (2 * NM - 4);
+            if constexpr (l0 >= 0 && l0 < 4)
+                l4[0][l0] = *(const f32x4 *)&srow[buf][0][l0 * 8 + g * 4];
+            if constexpr (l1 >= 0 && l1 < 4)
+                l4[1][l1] = *(const f32x4 *)&srow[buf][0][32 + l1 * 8 + g * 4];
+            mfma(n);
+            // one element pair every NM / 8 chunks, its P one chunk before its dS
+            constexpr int st8 = NM / 8;
+            constexpr int p0 = n - (NM + 1), p1 = n - (2 * NM + 1);
+            if constexpr (p0 >= 0 && p0 % st8 == 0 && p0 / st8 < 8)
+                soft_p(0, p0 / st8);
+            if constexpr (p0 >= 1 && (p0 - 1) % st8 == 0 && (p0 - 1) / st8 < 8)
+                soft_ds(0, (p0 - 1) / st8);
+            if constexpr (p1 >= 0 && p1 % st8 == 0 && p1 / st8 < 8)
+                soft_p(1, p1 / st8);
+            if constexpr (p1 >= 1 && (p1 - 1) % st8 == 0 && (p1 - 1) / st8 < 8)
+                soft_ds(1, (p1 - 1) / st8);
+            // the loads of the tile two steps ahead, spread over the step: a
+            // wave that issues them all at once waits for the address unit
+            // with its matrix pipe idle
+            constexpr int every = 4 * NM / kLoads;
+            if constexpr (n % every == 2 && n / every < kLoads)
+                stage_part(sg, n / every);
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
 
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    auto step = [&](int st, auto bufc) {
-        constexpr int buf = decltype(bufc)::value;
-        const bool next = st + 1 < nsteps;
-        if (next)
-            stage(st + 1, buf ^ 1);
-        int head, r0, nv;
-        step_rows(st, head, r0, nv);
-        // positions of the tile's first and last rows (ascending)
-        const int pmin = (MODE == kModeGlobal ? uni(sp[buf][0]) : r0) - base;
-        const int pmax = (MODE == kModeGlobal ? uni(sp[buf][nv - 1]) : r0 + nv - 1) - base;
-        // skip: no row of the tile sees a key of this wave
-        bool none = j0 >= T || pmax < j0;
-        if (MODE == kModeLocal)
-            none = none || pmin > jmax + w - 1;
-        if (!none) {
-            bool full = nv == kTileRows && pmin >= j0 + 31 && j0 + 31 < T;
-            if (MODE == kModeLocal)
-                full = full && pmax <= j0 + w - 1;
-            compute(bufc, r0, nv, !full);
-        }
-        if (next)
-            commit(buf ^ 1);
-        dma_wait_barrier();
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+    // Steps: the tiles from the last to the first, each for every head of the
+    // group, so that all key blocks of a KV head walk the same rows at the
+    // same time and find them in L2 (half
+    // of the L2 misses of the ascending order, heads outermost).  Each step stages the tile two
+    // steps ahead, runs `work` on its own and then waits for the next one's.
+    int st = 0, buf = 0, buf2 = 2;
+    auto step = [&](int hh, int q, auto &&work) __attribute__((always_inline)) {
+        const bool more = st + 2 < nsteps;
+        // two (tile, head) pairs on: hh + 2 < 2 G, or 2 for G = 1; past the
+        // last one the loads repeat its tile into a buffer no one reads
+        const int h2 = hh + 2, up = h2 < a.group ? 0 : (h2 < 2 * a.group ? 1 : 2);
+        const Stage sg = more ? stage_of(h2 - up * a.group, q - up, buf2) : stage_of(hh, q, buf2);
+        work(sg);
+        dma_wait_barrier_but<kLoads>();
+        st++;
+        buf = buf == kBufs - 1 ? 0 : buf + 1;
+        buf2 = buf2 == kBufs - 1 ? 0 : buf2 + 1;
     };
-    if (nsteps > 0) {
-        stage(0, 0);
-        commit(0);
-        dma_wait_barrier();
+    if (nsteps > 0)
+        stage_all(stage_of(0, nblk - 1, 0));
+    if (nsteps > 1) {
+        stage_all(stage_of(a.group > 1 ? 1 : 0, a.group > 1 ? nblk - 1 : nblk - 2, 1));
+        dma_wait_barrier_but<kLoads>();
+    } else {
+        dma_wait_barrier_but<0>();
     }
-    for (int st = 0; st < nsteps; st += 2) {
-        step(st, I0{});
-        if (st + 1 < nsteps)
-            step(st + 1, I1{});
-    }
+    // Loops of a single kind each, so that no loop body switches between
+    // instantiations (which would copy the 2 x D / 2 accumulators).
+    int q = nblk - 1;
+    for (; q > ql || (q >= 0 && qf >= nblk); q--)
+        for (int hh = 0; hh < a.group; hh++)
+            step(hh, q, stage_all);
+    for (; q >= qb && q >= qf; q--)
+        for (int hh = 0; hh < a.group; hh++)
+            step(hh, q, [&](const Stage &sg) __attribute__((always_inline)) { compute(buf, q, sg, T_{}); });
+    for (; q >= qa; q--)
+        for (int hh = 0; hh < a.group; hh++)
+            step(hh, q, [&](const Stage &sg) __attribute__((always_inline)) { compute(buf, q, sg, F_{}); });
+    for (; q >= qf; q--)
+        for (int hh = 0; hh < a.group; hh++)
+            step(hh, q, [&](const Stage &sg) __attribute__((always_inline)) { compute(buf, q, sg, T_{}); });
+    for (; q >= 0; q--)
+        for (int hh = 0; hh < a.group; hh++)
+            step(hh, q, stage_all);
+    // no load may be in flight to this workgroup's LDS when it ends
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
 
     if (key >= T)
         return;
@@ -700,7 +852,7 @@ __global__ __launch_bounds__(256) void fusion_bwd_kernel(const FusionBwdArgs a) 
                 uint16_t *dst = (br ? a.dog : a.dol) + (row * a.hq + h) * D + c0;
                 *(u32x4 *)dst = dob;
                 if (lead)
-                    (br ? a.delta_g : a.delta_l)[(int64_t)h * (br ? a.cap : a.n) + row] = dl;
+                    (br ? a.ndelta_g : a.ndelta_l)[(int64_t)h * (br ? a.cap : a.n) + row] = -dl;
                 if (br == 1)
                     *(u32x4 *)(a.qc + (row * a.hq + h) * D + c0) = *(const u32x4 *)(a.q_g + e0);
             }
@@ -761,12 +913,12 @@ __global__ __launch_bounds__(256) void gain_grad_kernel(int rows, int cols, cons
             (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// Delta = rowsum(dO * O) per (token, head) for plain attention (bf16 O and
+// -Delta = -rowsum(dO * O) per (token, head) for plain attention (bf16 O and
 // dO), written [Hq][N]; one thread per 8 elements, d / 8 lanes per row.
 template <int D>
 __global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_rows, int hq, int64_t n,
                                                          const uint16_t *o, const uint16_t *dout,
-                                                         float *delta) {
+                                                         float *ndelta) {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t row = g / (D / 8);
     const bool ok = row < n_rows;
@@ -784,12 +936,12 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_rows, int hq,
     if (ok && (g % (D / 8)) == 0) {
         const int64_t t = row / hq;
         const int h = (int)(row % hq);
-        delta[(int64_t)h * n + t] = acc;
+        ndelta[(int64_t)h * n + t] = -acc;
     }
 }
 
 // Inputs of the standalone query-sparse backward: per (selected rank < the
-// device count, head) row, the compact copy of the row of Q and Delta = dO . O (O fp32,
+// device count, head) row, the compact copy of the row of Q and -Delta = -dO . O (O fp32,
 // dO bf16, both compact), written [Hq][cap].  d / 8 lanes per row.
 template <int D>
 __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq, int64_t cap,
@@ -797,7 +949,7 @@ __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq
                                                           const int32_t *sel_idx,
                                                           const uint16_t *q, const float *o,
                                                           const uint16_t *dout, uint16_t *qc,
-                                                          float *delta) {
+                                                          float *ndelta) {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t row = g / (D / 8);
     // rows of ranks at or past the selected count (read on the device) are
@@ -823,7 +975,7 @@ __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq
     }
     acc = row_sum<D>(acc);
     if (ok && (g % (D / 8)) == 0)
-        delta[(int64_t)(row % hq) * cap + row / hq] = acc;
+        ndelta[(int64_t)(row % hq) * cap + row / hq] = -acc;
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(int64_t n, float *x) {
@@ -891,33 +1043,33 @@ hipError_t launch_gain_grad(int rows, int cols, const float *part, float *tmp, f
 }
 
 hipError_t launch_attn_delta(int64_t n, int hq, int head_dim, const uint16_t *o,
-                             const uint16_t *dout, float *delta, hipStream_t s) {
+                             const uint16_t *dout, float *ndelta, hipStream_t s) {
     const int64_t threads = n * hq * (head_dim / 8);
     if (threads <= 0)
         return hipSuccess;
     const dim3 grid((unsigned)((threads + 255) / 256));
     if (head_dim == 128)
         hipLaunchKernelGGL((attn_delta_kernel<128>), grid, dim3(256), 0, s, n * hq, hq, n, o, dout,
-                           delta);
+                           ndelta);
     else
         hipLaunchKernelGGL((attn_delta_kernel<64>), grid, dim3(256), 0, s, n * hq, hq, n, o, dout,
-                           delta);
+                           ndelta);
     return hipGetLastError();
 }
 
 hipError_t launch_sparse_prep(int64_t cap, int hq, int head_dim, const int32_t *n_sel_dev,
                               const int32_t *sel_idx, const uint16_t *q, const float *o,
-                              const uint16_t *dout, uint16_t *qc, float *delta, hipStream_t s) {
+                              const uint16_t *dout, uint16_t *qc, float *ndelta, hipStream_t s) {
     const int64_t threads = cap * hq * (head_dim / 8);
     if (threads <= 0)
         return hipSuccess;
     const dim3 grid((unsigned)((threads + 255) / 256));
     if (head_dim == 128)
         hipLaunchKernelGGL((sparse_prep_kernel<128>), grid, dim3(256), 0, s, cap * hq, hq, cap,
-                           n_sel_dev, sel_idx, q, o, dout, qc, delta);
+                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta);
     else
         hipLaunchKernelGGL((sparse_prep_kernel<64>), grid, dim3(256), 0, s, cap * hq, hq, cap,
-                           n_sel_dev, sel_idx, q, o, dout, qc, delta);
+                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta);
     return hipGetLastError();
 }
 

@@ -1308,8 +1308,8 @@ logo_status logo_attn_bwd(const logo_problem *p, const logo_bf16 *q, const logo_
     f.dol = (uint16_t *)(base + w.dol);
     f.dog = (uint16_t *)(base + w.dog);
     f.qc = (uint16_t *)(base + w.qc);
-    f.delta_l = (float *)(base + w.delta_l);
-    f.delta_g = (float *)(base + w.delta_g);
+    f.ndelta_l = (float *)(base + w.delta_l);
+    f.ndelta_g = (float *)(base + w.delta_g);
     f.side = (float *)(base + w.side);
     f.part_l = dgain_local ? (float *)(base + w.part_l) : nullptr;
     f.part_g = dgain_global ? (float *)(base + w.part_g) : nullptr;
@@ -1332,7 +1332,7 @@ logo_status logo_attn_bwd(const logo_problem *p, const logo_bf16 *q, const logo_
     a.v = v;
     a.dout = f.dol;
     a.lse = lse_local;
-    a.delta = f.delta_l;
+    a.ndelta = f.ndelta_l;
     a.row_stride = N;
     a.sel_idx = sel_idx;
     a.cu_sel = cu_sel;
@@ -1362,7 +1362,7 @@ logo_status logo_attn_bwd(const logo_problem *p, const logo_bf16 *q, const logo_
     a.v = v_g ? v_g : v;
     a.dout = f.dog;
     a.lse = lse_global;
-    a.delta = f.delta_g;
+    a.ndelta = f.ndelta_g;
     a.row_stride = cap;
     a.dq = dq_g ? dq_g : dq;
     a.dk = dk_g ? dk_g : dk;
@@ -1394,8 +1394,8 @@ logo_status logo_dense_causal_attn_bwd(const logo_problem *p, const logo_bf16 *q
     if (N == 0)
         return LOGO_OK;
     hipStream_t s = (hipStream_t)stream;
-    float *delta = (float *)ws;
-    st = hip_status(launch_attn_delta(N, p->num_q_heads, p->head_dim, out, dout, delta, s), s);
+    float *ndelta = (float *)ws;
+    st = hip_status(launch_attn_delta(N, p->num_q_heads, p->head_dim, out, dout, ndelta, s), s);
     if (st != LOGO_OK)
         return st;
     // plain causal attention is the local kernels' row set with a window that
@@ -1407,7 +1407,7 @@ logo_status logo_dense_causal_attn_bwd(const logo_problem *p, const logo_bf16 *q
     a.v = v;
     a.dout = dout;
     a.lse = lse;
-    a.delta = delta;
+    a.ndelta = ndelta;
     a.row_stride = N;
     a.dq = dq;
     a.dk = dk;
@@ -1478,11 +1478,11 @@ logo_status logo_global_attn_sparse_q_bwd(const logo_problem *p, const logo_bf16
     const int H = p->num_q_heads, d = p->head_dim;
     char *base = (char *)ws;
     uint16_t *qc = (uint16_t *)(base + w.qc);
-    float *delta = (float *)(base + w.delta);
+    float *ndelta = (float *)(base + w.delta);
     st = hip_status(launch_fill_zero((int64_t)N * H * d, dq, s), s);
     if (st == LOGO_OK && cap > 0)
         st = hip_status(launch_sparse_prep(cap, H, d, cu_sel + p->num_seqs, sel_idx, q, o_global,
-                                           dout, qc, delta, s),
+                                           dout, qc, ndelta, s),
                         s);
     if (st != LOGO_OK)
         return st;
@@ -1493,7 +1493,7 @@ logo_status logo_global_attn_sparse_q_bwd(const logo_problem *p, const logo_bf16
     a.v = v;
     a.dout = dout;
     a.lse = lse_global;
-    a.delta = delta;
+    a.ndelta = ndelta;
     a.row_stride = cap;
     a.sel_idx = sel_idx;
     a.cu_sel = cu_sel;

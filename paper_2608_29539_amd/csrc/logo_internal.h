@@ -258,11 +258,11 @@ hipError_t launch_branch_transform(int kind, int64_t n_rows, int H, int d, const
 // Backward pass (bwd.hip).  Rows of a branch: local = tokens (row index =
 // token), global = selected rows in rank order (row index = rank, token =
 // sel_idx[rank]).  q / dout are the branch's row-major [rows][Hq][d] bf16
-// tensors (the global branch uses the compact copy of Q^G), lse / delta are
-// [Hq][row_stride] fp32.  acc_*: add into the output instead of overwriting.
+// tensors (the global branch uses the compact copy of Q^G), lse and ndelta
+// (-Delta) are [Hq][row_stride] fp32.  acc_*: add into the output instead of overwriting.
 struct BwdArgs {
     const uint16_t *q, *k, *v, *dout;
-    const float *lse, *delta;
+    const float *lse, *ndelta;
     const int32_t *cu_seqlens, *sel_idx, *cu_sel;
     float *dq, *dk, *dv;
     int32_t num_seqs, hq, hkv, group, hpw, tpw, n_hg, window, ntile_max, cap;
@@ -279,7 +279,7 @@ struct FusionBwdArgs {
     float eps;
     int32_t n, hq, cap, tokens_per_block;
     uint16_t *dol, *dog, *qc;          // [N][Hq][d], [cap][Hq][d], [cap][Hq][d]
-    float *delta_l, *delta_g;          // [Hq][N], [Hq][cap]
+    float *ndelta_l, *ndelta_g;        // -Delta: [Hq][N], [Hq][cap]
     float *side;                       // [N][Hq]: row terms of dL/dp
     float *part_l, *part_g;            // gain-gradient partials or NULL
 };
@@ -292,13 +292,13 @@ int gain_grad_chunks(int rows);
 hipError_t launch_gain_grad(int rows, int cols, const float *part, float *tmp, float *out,
                             hipStream_t s);
 hipError_t launch_fill_zero(int64_t n, float *x, hipStream_t s);
-// Compact Q rows + Delta for the standalone query-sparse backward: ranks
+// Compact Q rows + -Delta for the standalone query-sparse backward: ranks
 // below min(n_sel_dev[0], cap) (the selected count, read on the device).
 hipError_t launch_sparse_prep(int64_t cap, int hq, int head_dim, const int32_t *n_sel_dev,
                               const int32_t *sel_idx, const uint16_t *q, const float *o,
-                              const uint16_t *dout, uint16_t *qc, float *delta, hipStream_t s);
+                              const uint16_t *dout, uint16_t *qc, float *ndelta, hipStream_t s);
 hipError_t launch_attn_delta(int64_t n, int hq, int head_dim, const uint16_t *o,
-                             const uint16_t *dout, float *delta, hipStream_t s);
+                             const uint16_t *dout, float *ndelta, hipStream_t s);
 hipError_t launch_bwd_dq(int mode, int head_dim, const BwdArgs &a, int grid, hipStream_t s);
 hipError_t launch_bwd_dkv(int mode, int head_dim, const BwdArgs &a, int grid, hipStream_t s);
 int bwd_keys_per_block();

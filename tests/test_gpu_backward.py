@@ -317,3 +317,16 @@ def test_backward_full_size_sampled(pk, name, n_sel_rows, n_uns_rows, n_keys):
     print(f"[bwd full] key-gradient sum / (sqrt(N) rms): max {float(zero_sum.max()):.3g}",
           flush=True)
     assert float(zero_sum.max()) <= 0.05
+
+
+@pytest.mark.parametrize("lens,G,d,win", [
+    # the dK/dV pipeline runs two (tile, head) steps ahead: one, two and three
+    # steps in all, with the tile edges of 32 keys, 64 rows and 128 keys
+    ((1,), 1, 128, 1), ((64,), 2, 128, 64), ((65,), 1, 64, 7), ((32, 33), 3, 128, 33),
+    ((127, 128, 129), 1, 128, 65), ((191, 193), 2, 64, 129), ((257,), 3, 64, 4096),
+    ((256, 320), 4, 128, 63),
+])
+@pytest.mark.parametrize("ratio", [0.0, 0.5, 1.0])
+def test_backward_pipeline_edges(pk, lens, G, d, win, ratio):
+    w = synth.small_workload(lens, 2 * G, 2, d, win, ratio, seed=5300 + sum(lens))
+    run_case(pk, w, ratio=ratio, distinct=G == 2, tag=f"edges G={G} r={ratio}")
