@@ -155,8 +155,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_attn_kernel(const DecodeAr
     const int k1 = min(L, k0 + a.kc);
     if (k0 >= k1)
         return;                                  // a chunk past this sequence's keys
-    // this item's partials: [item][GH][m, l, acc[D]]
-    float *out_part = (global ? a.part_global : a.part_local) + (int64_t)item * GH * (D + 2);
+    // this item's partials: acc [item][GH][D], then all items' m, l
+    float *out_part = (global ? a.part_global : a.part_local) + (int64_t)item * GH * D;
+    float *out_ml = (global ? a.part_global + (int64_t)a.n_global_items * GH * D
+                            : a.part_local + (int64_t)a.n_local_items * GH * D) +
+                    (int64_t)item * GH * 2;
     const uint16_t *kc_ = global ? a.k_g : a.k;
     const uint16_t *vc_ = global ? a.v_g : a.v;
     const uint16_t *qv = global ? a.q_g : a.q;
@@ -290,54 +293,77 @@ __global__ __launch_bounds__(kDecThreads) void decode_attn_kernel(const DecodeAr
             const float ab = s_acc[w2][hh][x];
             merge_into(M, Lw, mb, lb, &A, &ab, 1);
         }
-        float *op = out_part + hh * (D + 2);
-        op[2 + x] = A;
+        out_part[t] = A;
         if (x == 0) {
-            op[0] = M;
-            op[1] = Lw;
+            out_ml[2 * hh] = M;
+            out_ml[2 * hh + 1] = Lw;
         }
     }
 }
 
-// One wave per (sequence, query head), four per workgroup.  A branch's
-// chunks are merged in one pass: the largest chunk maximum first (lane c
-// holds chunk c), then every chunk's weight 2^(m_c - M), then the weighted
-// sum, in which the wave's lanes are 4 chunk groups x 16 element groups
-// (lane = 16 cg + eg: chunks cg, cg+4, ..., elements D/16 eg ..), so each
-// lane's dependent chain is a quarter of the chunks; two shuffle steps add
-// the chunk groups.  Lanes 0..15 then hold the row (D/16 elements each) for
-// ContextNorm, the fusion and the store.  At most 128 chunks per branch.
+// WPH waves per (sequence, query head), four waves per workgroup.  A branch's
+// chunks are merged in one pass: the largest chunk maximum first (lane c of
+// every wave holds chunks c and c + 64), then every chunk's weight
+// 2^(m_c - M), then the weighted sum, in which the head's threads are 4 WPH
+// chunk groups x 16 element groups (chunks cg, cg + 4 WPH, ..., D/16 elements
+// in 16-byte loads), so a thread's chain is that share of the chunks; shuffles
+// add a wave's four groups, LDS the waves.  Bound by the latency of that
+// chain: with WPH = 4 the merge of 64 chunks (16 caches of 32K tokens, 32
+// heads of d = 128) takes 6.6 us, with one wave per head and 4-byte loads it
+// took 8.6; with a few chunks per cache the one wave is the faster (a step of
+// 64 caches of 2K tokens 82.0 against 84.4 us), so the launcher takes WPH = 4
+// above 16 chunks.  At most 128 chunks per branch.
 constexpr int kMaxChunks = 128;
 
-template <int D>
+constexpr int kWideMergeChunks = 16;
+
+template <int D, int WPH>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const DecodeArgs a) {
-    constexpr int EL = D / 16;                    // elements per lane
-    __shared__ float s_w[4][kMaxChunks];
+    constexpr int EL = D / 16;                    // elements per thread
+    typedef float f32x4c __attribute__((ext_vector_type(4)));
+    __shared__ float s_w[4][2][kMaxChunks];
+    __shared__ __attribute__((aligned(16))) float s_o[2][4][D];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cg = lane >> 4, eg = lane & 15;
-    const int job = blockIdx.x * 4 + wave;
-    if (job >= a.num_seqs * a.hq)
+    const int cg = (wave % WPH) * 4 + (lane >> 4), eg = lane & 15;
+    const int job = blockIdx.x * (4 / WPH) + wave / WPH;
+    if (WPH == 1 && job >= a.num_seqs * a.hq)
         return;                                   // whole wave: no barrier below
     const int b = job / a.hq, h = job % a.hq;
     const int L = a.cu[b + 1] - a.cu[b];
     // chunks of this sequence (clamped to the planned slots: max_seqlen bounds L)
     const int n_loc = min((min(L, a.window) + a.kc - 1) / a.kc, a.chunks_local);
     const int n_glb = min((L + a.kc - 1) / a.kc, a.chunks_global);
-    const int r = a.rank_of[b];
     const float p = a.gate[b];
+    const bool sel = p > decode_threshold(a);
     const int kvh = h / a.group, hg = (h % a.group) / a.gh, hh = (h % a.group) % a.gh;
-    float *w = s_w[wave];
-    // O / l of one branch of sequence `row`; lane eg's elements
-    auto branch = [&](const float *parts, int row, int nch, int chunks_stride, float (&o)[EL]) {
-        const int64_t item0 = (((int64_t)row * a.hkv + kvh) * a.nhg + hg) * chunks_stride;
-        auto slot = [&](int c) { return parts + ((item0 + c) * a.gh + hh) * (D + 2); };
+    // This wave's share of one branch's sum of 2^(m_c - M) O_c, in A (every
+    // chunk group's lanes) and, for several waves, in s_o; returns the sum of
+    // the weighted l (the same in every thread).
+    auto branch = [&](int br, const float *parts, int64_t n_items, int nch, int chunks_stride,
+                      float (&A)[EL]) {
+        const int64_t item0 = (((int64_t)b * a.hkv + kvh) * a.nhg + hg) * chunks_stride;
+        const float *acc = parts + (item0 * a.gh + hh) * D + eg * EL;
+        const float *ml = parts + n_items * a.gh * D + (item0 * a.gh + hh) * 2;
+        float *w = s_w[wave][br];
+        // the first kPre chunks' elements are loaded before the weights exist
+        constexpr int kPre = 4, EV = EL / 4;
+        f32x4c pre[kPre][EV];
+#pragma unroll
+        for (int j = 0; j < kPre; j++) {
+            const int c = cg + j * 4 * WPH;
+            const float *pp = acc + (int64_t)c * a.gh * D;
+            if (c < nch)
+#pragma unroll
+                for (int i = 0; i < EV; i++)
+                    pre[j][i] = *(const f32x4c *)(pp + 4 * i);
+        }
         float mc[2], lc[2];
         float M = kNegInfD;
 #pragma unroll
         for (int i = 0; i < 2; i++) {
             const int c = lane + 64 * i;
-            mc[i] = c < nch ? slot(c)[0] : kNegInfD;
-            lc[i] = c < nch ? slot(c)[1] : 0.f;
+            mc[i] = c < nch ? ml[(int64_t)c * a.gh * 2] : kNegInfD;
+            lc[i] = c < nch ? ml[(int64_t)c * a.gh * 2 + 1] : 0.f;
             M = fmaxf(M, mc[i]);
         }
 #pragma unroll
@@ -349,8 +375,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const DecodeArgs a)
         for (int i = 0; i < 2; i++) {
             const int c = lane + 64 * i;
             const float wc = c < nch ? __builtin_amdgcn_exp2f(mc[i] - Mc) : 0.f;
-            if (c < nch)
-                w[c] = wc;
+            w[c] = wc;
             lsum = fmaf(wc, lc[i], lsum);
         }
 #pragma unroll
@@ -358,34 +383,62 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const DecodeArgs a)
             lsum += __shfl_xor(lsum, sh, 64);
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        float A[EL];
 #pragma unroll
         for (int i = 0; i < EL; i++)
             A[i] = 0.f;
-#pragma unroll 2
-        for (int c = cg; c < nch; c += 4) {
-            const float wc = w[c];
-            const float *pp = slot(c) + 2 + eg * EL;
+        auto add = [&](float wc, int i, const f32x4c v) {
 #pragma unroll
-            for (int i = 0; i < EL; i++)
-                A[i] = fmaf(wc, pp[i], A[i]);
+            for (int e = 0; e < 4; e++)
+                A[4 * i + e] = fmaf(wc, v[e], A[4 * i + e]);
+        };
+#pragma unroll
+        for (int j = 0; j < kPre; j++) {
+            const int c = cg + j * 4 * WPH;
+            if (c < nch) {
+                const float wc = w[c];
+#pragma unroll
+                for (int i = 0; i < EV; i++)
+                    add(wc, i, pre[j][i]);
+            }
+        }
+#pragma unroll 2
+        for (int c = cg + kPre * 4 * WPH; c < nch; c += 4 * WPH) {
+            const float wc = w[c];
+            const float *pp = acc + (int64_t)c * a.gh * D;
+#pragma unroll
+            for (int i = 0; i < EV; i++)
+                add(wc, i, *(const f32x4c *)(pp + 4 * i));
         }
 #pragma unroll
         for (int i = 0; i < EL; i++) {
             A[i] += __shfl_xor(A[i], 16, 64);
             A[i] += __shfl_xor(A[i], 32, 64);
+            if (WPH > 1 && lane < 16)
+                s_o[br][wave][eg * EL + i] = A[i];
         }
-        __builtin_amdgcn_wave_barrier();
-        const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-#pragma unroll
-        for (int i = 0; i < EL; i++)
-            o[i] = A[i] * inv;
+        return lsum;
     };
-    auto norm = [&](float (&o)[EL], const float *gain) {
+    float ol[EL], og[EL];
+    const float l_loc = branch(0, a.part_local, a.n_local_items, n_loc, a.chunks_local, ol);
+    float l_glb = 0.f;
+    if (sel)                                      // (every wave of the head)
+        l_glb = branch(1, a.part_global, a.n_global_items, n_glb, a.chunks_global, og);
+    if constexpr (WPH > 1)
+        __syncthreads();
+    if (wave % WPH != 0 || lane >= 16)
+        return;
+    // the row's D values in 16 lanes: O / l, ContextNorm
+    auto norm = [&](int br, float lsum, const float *gain, float (&o)[EL]) {
+        const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
         float ss = 0.f;
 #pragma unroll
-        for (int i = 0; i < EL; i++)
+        for (int i = 0; i < EL; i++) {
+            [[maybe_unused]] const int x = eg * EL + i;
+            if constexpr (WPH == 4)
+                o[i] = (s_o[br][0][x] + s_o[br][1][x]) + (s_o[br][2][x] + s_o[br][3][x]);
+            o[i] *= inv;
             ss = fmaf(o[i], o[i], ss);
+        }
 #pragma unroll
         for (int sh = 1; sh < 16; sh <<= 1)
             ss += __shfl_xor(ss, sh, 64);
@@ -394,19 +447,13 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const DecodeArgs a)
         for (int i = 0; i < EL; i++)
             o[i] = o[i] * rn * (gain ? gain[h * D + eg * EL + i] : 1.f);
     };
-    float ol[EL];
-    branch(a.part_local, b, n_loc, a.chunks_local, ol);
-    norm(ol, a.gain_local);
-    if (r >= 0) {
-        float og[EL];
-        branch(a.part_global, b, n_glb, a.chunks_global, og);
-        norm(og, a.gain_global);
+    norm(0, l_loc, a.gain_local, ol);
+    if (sel) {
+        norm(1, l_glb, a.gain_global, og);
 #pragma unroll
         for (int i = 0; i < EL; i++)
             ol[i] = (1.f - p) * ol[i] + p * og[i];
     }
-    if (cg != 0)
-        return;
     uint16_t *op = a.out + ((int64_t)b * a.hq + h) * D + eg * EL;
 #pragma unroll
     for (int i = 0; i < EL; i++)
@@ -435,11 +482,20 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s) {
     hipError_t e = a.head_dim == 128 ? launch_attn_d<128>(a, s) : launch_attn_d<64>(a, s);
     if (e != hipSuccess)
         return e;
-    const int grid = (a.num_seqs * a.hq + 3) / 4;
-    if (a.head_dim == 128)
-        hipLaunchKernelGGL((decode_combine_kernel<128>), dim3(grid), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((decode_combine_kernel<64>), dim3(grid), dim3(256), 0, s, a);
+    const int jobs = a.num_seqs * a.hq;
+    const bool wide = a.chunks_global > kWideMergeChunks;
+    const dim3 grid(wide ? jobs : (jobs + 3) / 4);
+    if (a.head_dim == 128) {
+        if (wide)
+            hipLaunchKernelGGL((decode_combine_kernel<128, 4>), grid, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((decode_combine_kernel<128, 1>), grid, dim3(256), 0, s, a);
+    } else {
+        if (wide)
+            hipLaunchKernelGGL((decode_combine_kernel<64, 4>), grid, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((decode_combine_kernel<64, 1>), grid, dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 

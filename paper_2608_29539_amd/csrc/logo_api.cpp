@@ -174,9 +174,6 @@ FwdWs fwd_ws(const logo_problem *p, int32_t cap, bool aperm = false) {
     return w;
 }
 
-// Decoding: keys per chunk (a multiple of 32, at least 256, at most 128
-// chunks per cache), query heads per work item (the largest of 4, 2, 1
-// dividing the group), and the workspace of the partial results.
 // logo_attn_bwd: dO^L / dO^G (bf16), the compact Q^G rows, the row sums
 // Delta, the per-row gate terms and the gain-gradient partials.
 constexpr int kFusionBwdMaxBlocks = 2048;
@@ -255,6 +252,9 @@ BwdArgs make_bwd_args(const logo_problem *p) {
     return a;
 }
 
+// Decoding: keys per chunk (a multiple of 32, at least 128, at most 128
+// chunks per cache), query heads per work item (the largest of 4, 2, 1
+// dividing the group), and the workspace of the partial results.
 struct DecodePlan {
     int kc, gh, nhg, chunks_local, chunks_global;
     long long n_local_items, n_global_items;
@@ -263,7 +263,7 @@ struct DecodePlan {
 DecodePlan decode_plan(const logo_problem *p) {
     DecodePlan d;
     const long long maxL = p->max_seqlen > 0 ? p->max_seqlen : 1;
-    // Keys per chunk: at least 512 (a workgroup's fixed cost -- query loads,
+    // Keys per chunk: 512 or more (a workgroup's fixed cost -- query loads,
     // stream and wave merges, the partial's store -- is then small next to
     // its 256 KiB of K / V per KV head at d = 128), at most 128 chunks per
     // cache, a multiple of 32.
@@ -277,6 +277,20 @@ DecodePlan decode_plan(const logo_problem *p) {
     d.chunks_local = (int)((wl + d.kc - 1) / d.kc);
     d.chunks_global = (int)((maxL + d.kc - 1) / d.kc);
     const long long per_row = (long long)p->num_kv_heads * d.nhg;
+    // Few caches: shorter chunks while the step has fewer than 1024 work
+    // items (four workgroups per CU) and a cache at most 32 chunks, since
+    // then a workgroup's serial walk over its keys sets the time.  One cache
+    // of 4K tokens, 32 / 8 heads: 22.6 -> 15.8 us per step with 128-key
+    // chunks (64: 18.1); four of 8K tokens, 8 heads: 27.4 -> 25.3.  Past
+    // that: 16 caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with
+    // shorter ones, one cache of 32K tokens 36.3 with 512 and 44.9 with 256.
+    // (The partial results of such a step stay under 5 MB.)
+    while (d.kc > 128 && (maxL + d.kc / 2 - 1) / (d.kc / 2) <= 32 &&
+           p->num_seqs * per_row * (d.chunks_local + d.chunks_global) < 1024) {
+        d.kc /= 2;
+        d.chunks_local = (int)((wl + d.kc - 1) / d.kc);
+        d.chunks_global = (int)((maxL + d.kc - 1) / d.kc);
+    }
     d.n_local_items = (long long)p->num_seqs * per_row * d.chunks_local;
     d.n_global_items = (long long)p->num_seqs * per_row * d.chunks_global;
     const size_t slot = sizeof(float) * (size_t)d.gh * (p->head_dim + 2);

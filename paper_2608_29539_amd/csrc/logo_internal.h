@@ -223,7 +223,7 @@ hipError_t launch_select(const int32_t *cu_seqlens, int num_seqs, int max_seqlen
 
 // One decoding step (decode.hip).  Work items: local (sequence, KV head,
 // head group, chunk) then global (selected rank, KV head, head group,
-// chunk); partials [item][gh][m, l, acc[d]].
+// chunk); partials acc [item][gh][d], then m, l [item][gh][2].
 struct DecodeArgs {
     const uint16_t *q, *k, *v;       // q: [B][Hq][d] new tokens; k, v: caches [N][Hkv][d]
     const uint16_t *q_g, *k_g, *v_g; // global-branch tensors (aliases when not given)

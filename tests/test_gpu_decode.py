@@ -163,3 +163,17 @@ def test_decode_deterministic(pk):
     b = pk.logo_decode(prob, dev["q"], dev["k"], dev["v"], dev["gate"], threshold=0.0)[0]
     torch.cuda.synchronize()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,win", [
+    # the longest cache sets the chunks: 128-key chunks up to 32 of them, then
+    # 256 and 512 keys; more than 16 chunks are merged by four waves a head
+    ((127, 128, 129), 3, 1, 128, 128), ((2048,), 4, 4, 64, 100), ((2049, 5), 8, 2, 128, 2000),
+    ((4096, 4095), 4, 2, 64, 4096), ((4097,), 4, 4, 128, 300), ((8193, 1), 8, 8, 128, 600),
+    ((16385,), 4, 1, 64, 16385), ((40000, 130), 2, 1, 128, 129),
+    ((300,) * 40, 16, 8, 64, 200),            # too many items for shorter chunks
+])
+def test_decode_chunk_rules(pk, lens, hq, hkv, d, win):
+    w = synth.small_workload(lens, hq, hkv, d, win, 0.0, seed=3300 + sum(lens))
+    for thr in (-math.inf, 0.5):
+        run_case(pk, w, thr, gains=True, tag=f"chunks {lens[0]} thr={thr}")
