@@ -187,17 +187,24 @@ class Problem:
         return ctypes.byref(self._c)
 
 
-def _stream():
+def _stream() -> int:
+    """The raw handle of torch's current stream on the current device (without
+    the Stream object, which takes 2 us of a call's 10-12 us in Python)."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and torch.cuda.is_initialized():
+        return raw(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
-def _ptr(t) -> Optional[ctypes.c_void_p]:
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _check(t, dtype, shape, name):
-    import torch
+    if (t is not None and t.dtype == dtype and t.is_cuda and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t
     if t is None:
         raise ValueError(f"{name} is required")
     if t.dtype != dtype:
@@ -212,12 +219,13 @@ def _check(t, dtype, shape, name):
 
 
 def _ws(prob: Problem, entry: int, cap: int, ws):
+    if ws is not None:
+        return ws, ws.numel()       # (the entry point refuses one that is too small)
     import torch
     need = library().logo_workspace_bytes(prob.c, entry, cap)
     if need == 0:
         return None, 0
-    if ws is None:
-        ws = torch.empty(need, dtype=torch.uint8, device=prob.cu_seqlens.device)
+    ws = torch.empty(need, dtype=torch.uint8, device=prob.cu_seqlens.device)
     return ws, int(ws.numel())
 
 
