@@ -8,8 +8,8 @@
 //                      Delta = dO . O, each row's term of dL/dp, partial gain
 //                      gradients, and a compact copy of the selected rows of
 //                      Q^G (so the global branch's query tiles are contiguous).
-//   gate_grad_kernel   dL/dp_t = sum over heads of the row terms.
-//   gain_grad_kernel   column sums of the gain-gradient partials.
+//   bwd_reduce_kernel  dL/dp_t = sum over heads of the row terms, column sums
+//                      of the gain-gradient partials, the zeros of dq_g.
 //   bwd_dq_kernel      dQ of one branch.  Rows: local = every token (keys of
 //                      its window), global = the selected rows in rank order
 //                      (keys 0..pos).  Lane = query: S^T = K Q^T and
@@ -879,38 +879,68 @@ __global__ __launch_bounds__(256) void fusion_bwd_kernel(const FusionBwdArgs a) 
     }
 }
 
-// dL/dp_t: sum over heads of the per-row terms (zero for unselected tokens).
-__global__ __launch_bounds__(256) void gate_grad_kernel(int n, int hq, const float *side,
-                                                        float *dgate) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= n)
-        return;
-    float s = 0.f;
-    for (int h = 0; h < hq; h++)
-        s += side[(int64_t)t * hq + h];
-    dgate[t] = s;
+// Zeros, 16 bytes per thread and step (block blk of the range; n a multiple
+// of 4, x 16-byte aligned).
+constexpr int kZeroPerBlock = 256 * 4 * 4;
+__device__ __forceinline__ void zero_block(float *x, int64_t n, int64_t blk) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int64_t i = blk * kZeroPerBlock + (j * 256 + threadIdx.x) * 4;
+        if (i < n)
+            *(f32x4 *)(x + i) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 }
 
-// Column sums of [rows][cols] partials over row chunks of kGainChunk:
-// workgroup (x, y) sums rows y*kGainChunk .. +kGainChunk-1 of 64 columns
-// (the 4 waves take every 4th row, then a fixed-order sum of the 4) into
-// out[y][cols].  Two passes reduce any row count to one row.
+// What follows the ContextNorm + fusion backward, in one launch (its parts
+// are independent, and as five launches of 4-8 us each they cost a small
+// training step more than its dQ kernel).  Workgroups in this order:
+//   gate_blocks   dL/dp_t: sum over heads of the per-row terms (zero for
+//                 unselected tokens), one token per thread
+//   gain blocks   column sums of the [rows][cols] gain-gradient partials of
+//                 each branch with an output, over row chunks of kGainChunk:
+//                 workgroup (x, y) sums rows y*kGainChunk .. of 64 columns (the
+//                 4 waves take every 4th row, then a fixed-order sum of the
+//                 4) into row y of `out`.  Two passes reduce any row count up
+//                 to kGainChunk^2 to one row.
+//   zero_blocks   dq_g, which the global branch's dQ writes only at the
+//                 selected rows
 constexpr int kGainChunk = 64;
-__global__ __launch_bounds__(256) void gain_grad_kernel(int rows, int cols, const float *part,
-                                                        float *out) {
+__global__ __launch_bounds__(256) void bwd_reduce_kernel(const BwdReduceArgs a) {
     __shared__ float red[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * 64 + lane;
-    const int r0 = blockIdx.y * kGainChunk, r1 = min(rows, r0 + kGainChunk);
-    float s = 0.f;
-    if (col < cols)
-        for (int r = r0 + wave; r < r1; r += 4)
-            s += part[(int64_t)r * cols + col];
-    red[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && col < cols)
-        out[(int64_t)blockIdx.y * cols + col] =
-            (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    int blk = blockIdx.x;
+    if (blk < a.gate_blocks) {
+        const int t = blk * 256 + threadIdx.x;
+        if (t < a.n) {
+            float s = 0.f;
+            for (int h = 0; h < a.hq; h++)
+                s += a.side[(int64_t)t * a.hq + h];
+            a.dgate[t] = s;
+        }
+        return;
+    }
+    blk -= a.gate_blocks;
+    const int col_blocks = (a.cols + 63) / 64;
+    for (int br = 0; br < 2; br++) {
+        if (!a.out[br])
+            continue;
+        if (blk < col_blocks * a.chunks) {
+            const int y = blk / col_blocks, col = (blk % col_blocks) * 64 + lane;
+            const int r0 = y * kGainChunk, r1 = min(a.rows, r0 + kGainChunk);
+            float s = 0.f;
+            if (col < a.cols)
+                for (int r = r0 + wave; r < r1; r += 4)
+                    s += a.part[br][(int64_t)r * a.cols + col];
+            red[wave][lane] = s;
+            __syncthreads();
+            if (wave == 0 && col < a.cols)
+                a.out[br][(int64_t)y * a.cols + col] =
+                    (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+            return;
+        }
+        blk -= col_blocks * a.chunks;
+    }
+    zero_block(a.zero, a.n_zero, blk);
 }
 
 // -Delta = -rowsum(dO * O) per (token, head) for plain attention (bf16 O and
@@ -940,7 +970,9 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_rows, int hq,
     }
 }
 
-// Inputs of the standalone query-sparse backward: per (selected rank < the
+// Inputs of the standalone query-sparse backward (and, in the workgroups from
+// prep_blocks on, the zeros of dq, which dQ writes only at the selected rows;
+// one launch, 33 -> 22 us at 8192 of 16384 rows of 8 heads, d = 128): per (selected rank < the
 // device count, head) row, the compact copy of the row of Q and -Delta = -dO . O (O fp32,
 // dO bf16, both compact), written [Hq][cap].  d / 8 lanes per row.
 template <int D>
@@ -949,7 +981,12 @@ __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq
                                                           const int32_t *sel_idx,
                                                           const uint16_t *q, const float *o,
                                                           const uint16_t *dout, uint16_t *qc,
-                                                          float *ndelta) {
+                                                          float *ndelta, int64_t prep_blocks,
+                                                           float *zero, int64_t n_zero) {
+    if (blockIdx.x >= prep_blocks) {
+        zero_block(zero, n_zero, blockIdx.x - prep_blocks);
+        return;
+    }
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t row = g / (D / 8);
     // rows of ranks at or past the selected count (read on the device) are
@@ -976,12 +1013,6 @@ __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq
     acc = row_sum<D>(acc);
     if (ok && (g % (D / 8)) == 0)
         ndelta[(int64_t)(row % hq) * cap + row / hq] = -acc;
-}
-
-__global__ __launch_bounds__(256) void fill_zero_kernel(int64_t n, float *x) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n)
-        x[i] = 0.f;
 }
 
 template <int D>
@@ -1016,29 +1047,51 @@ hipError_t launch_fusion_bwd(const FusionBwdArgs &a, int grid, int head_dim, hip
                            : launch_fusion_bwd_d<64>(a, grid, s);
 }
 
-hipError_t launch_gate_grad(int n, int hq, const float *side, float *dgate, hipStream_t s) {
-    if (n <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(gate_grad_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, hq, side,
-                       dgate);
-    return hipGetLastError();
-}
-
 int gain_grad_chunks(int rows) { return (rows + kGainChunk - 1) / kGainChunk; }
 
-hipError_t launch_gain_grad(int rows, int cols, const float *part, float *tmp, float *out,
-                            hipStream_t s) {
-    const int chunks = gain_grad_chunks(rows);
-    if (chunks > kGainChunk)
+// tmp[br]: gain_grad_chunks(rows) x cols floats for each branch with an
+// output (dgain[br] not NULL); dgate and zero may be NULL.
+hipError_t launch_bwd_reduce(int n, int hq, const float *side, float *dgate, int rows, int cols,
+                             const float *const part[2], float *const tmp[2],
+                             float *const dgain[2], float *zero, int64_t n_zero, hipStream_t s) {
+    BwdReduceArgs a;
+    a.n = n;
+    a.hq = hq;
+    a.side = side;
+    a.dgate = dgate;
+    a.gate_blocks = dgate ? (n + 255) / 256 : 0;
+    a.rows = rows;
+    a.cols = cols;
+    a.chunks = gain_grad_chunks(rows);
+    if (a.chunks > kGainChunk)
         return hipErrorInvalidValue;               // two passes cover 4096 rows
-    const float *src = part;
-    if (chunks > 1) {
-        hipLaunchKernelGGL(gain_grad_kernel, dim3((cols + 63) / 64, chunks), dim3(256), 0, s, rows,
-                           cols, part, tmp);
-        src = tmp;
+    a.zero = zero;
+    a.n_zero = zero ? n_zero : 0;
+    const long long per_branch = (long long)((cols + 63) / 64) * a.chunks;
+    long long grid = a.gate_blocks + (a.n_zero + kZeroPerBlock - 1) / kZeroPerBlock;
+    for (int br = 0; br < 2; br++) {
+        a.part[br] = part[br];
+        a.out[br] = dgain[br] ? (a.chunks > 1 ? tmp[br] : dgain[br]) : nullptr;
+        if (a.out[br])
+            grid += per_branch;
     }
-    hipLaunchKernelGGL(gain_grad_kernel, dim3((cols + 63) / 64, 1), dim3(256), 0, s,
-                       chunks > 1 ? chunks : rows, cols, src, out);
+    if (grid == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)grid), dim3(256), 0, s, a);
+    if (a.chunks > 1 && (dgain[0] || dgain[1])) {
+        grid = 0;
+        for (int br = 0; br < 2; br++) {
+            a.part[br] = tmp[br];
+            a.out[br] = dgain[br];
+            if (dgain[br])
+                grid += (cols + 63) / 64;
+        }
+        a.gate_blocks = 0;
+        a.n_zero = 0;
+        a.rows = a.chunks;
+        a.chunks = 1;
+        hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)grid), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1059,24 +1112,19 @@ hipError_t launch_attn_delta(int64_t n, int hq, int head_dim, const uint16_t *o,
 
 hipError_t launch_sparse_prep(int64_t cap, int hq, int head_dim, const int32_t *n_sel_dev,
                               const int32_t *sel_idx, const uint16_t *q, const float *o,
-                              const uint16_t *dout, uint16_t *qc, float *ndelta, hipStream_t s) {
-    const int64_t threads = cap * hq * (head_dim / 8);
-    if (threads <= 0)
+                              const uint16_t *dout, uint16_t *qc, float *ndelta, float *zero,
+                              int64_t n_zero, hipStream_t s) {
+    const int64_t prep = (cap * hq * (head_dim / 8) + 255) / 256;
+    const int64_t blocks = prep + (n_zero + kZeroPerBlock - 1) / kZeroPerBlock;
+    if (blocks <= 0)
         return hipSuccess;
-    const dim3 grid((unsigned)((threads + 255) / 256));
+    const dim3 grid((unsigned)blocks);
     if (head_dim == 128)
         hipLaunchKernelGGL((sparse_prep_kernel<128>), grid, dim3(256), 0, s, cap * hq, hq, cap,
-                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta);
+                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta, prep, zero, n_zero);
     else
         hipLaunchKernelGGL((sparse_prep_kernel<64>), grid, dim3(256), 0, s, cap * hq, hq, cap,
-                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_zero(int64_t n, float *x, hipStream_t s) {
-    if (n <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, x);
+                           n_sel_dev, sel_idx, q, o, dout, qc, ndelta, prep, zero, n_zero);
     return hipGetLastError();
 }
 

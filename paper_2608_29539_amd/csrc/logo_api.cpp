@@ -178,7 +178,7 @@ FwdWs fwd_ws(const logo_problem *p, int32_t cap, bool aperm = false) {
 // Delta, the per-row gate terms and the gain-gradient partials.
 constexpr int kFusionBwdMaxBlocks = 2048;
 struct BwdWs {
-    size_t dol, dog, qc, delta_l, delta_g, side, part_l, part_g, part_tmp, total;
+    size_t dol, dog, qc, delta_l, delta_g, side, part_l, part_g, part_tmp, tmp_stride, total;
     int blocks, tokens_per_block, part_rows;
 };
 BwdWs bwd_ws(const logo_problem *p, int32_t cap) {
@@ -211,7 +211,8 @@ BwdWs bwd_ws(const logo_problem *p, int32_t cap) {
     w.part_g = off;
     off += align_up(4 * (size_t)w.part_rows * H * d);
     w.part_tmp = off;
-    off += align_up(4 * (size_t)gain_grad_chunks(w.part_rows) * H * d);
+    w.tmp_stride = align_up(4 * (size_t)gain_grad_chunks(w.part_rows) * H * d);
+    off += 2 * w.tmp_stride;                   // one per branch
     w.total = off;
     return w;
 }
@@ -1328,13 +1329,14 @@ logo_status logo_attn_bwd(const logo_problem *p, const logo_bf16 *q, const logo_
     f.part_l = dgain_local ? (float *)(base + w.part_l) : nullptr;
     f.part_g = dgain_global ? (float *)(base + w.part_g) : nullptr;
     st = hip_status(launch_fusion_bwd(f, w.blocks, d, s), s);
-    if (st == LOGO_OK && dgate)
-        st = hip_status(launch_gate_grad(N, H, f.side, dgate, s), s);
-    float *gtmp = (float *)(base + w.part_tmp);
-    if (st == LOGO_OK && dgain_local)
-        st = hip_status(launch_gain_grad(w.part_rows, H * d, f.part_l, gtmp, dgain_local, s), s);
-    if (st == LOGO_OK && dgain_global)
-        st = hip_status(launch_gain_grad(w.part_rows, H * d, f.part_g, gtmp, dgain_global, s), s);
+    if (st != LOGO_OK)
+        return st;
+    const float *part[2] = {f.part_l, f.part_g};
+    float *tmp[2] = {(float *)(base + w.part_tmp), (float *)(base + w.part_tmp + w.tmp_stride)};
+    float *dgain[2] = {dgain_local, dgain_global};
+    st = hip_status(launch_bwd_reduce(N, H, f.side, dgate, w.part_rows, H * d, part, tmp, dgain,
+                                      dq_g, (int64_t)N * H * d, s),
+                    s);
     if (st != LOGO_OK)
         return st;
 
@@ -1367,10 +1369,6 @@ logo_status logo_attn_bwd(const logo_problem *p, const logo_bf16 *q, const logo_
 
     // 3. global branch: selected rows (compact), dense K/V; added into the
     //    local gradients where the branch shares the tensor
-    if (dq_g)
-        st = hip_status(launch_fill_zero((int64_t)N * H * d, dq_g, s), s);
-    if (st != LOGO_OK)
-        return st;
     a.q = f.qc;
     a.k = k_g ? k_g : k;
     a.v = v_g ? v_g : v;
@@ -1493,11 +1491,9 @@ logo_status logo_global_attn_sparse_q_bwd(const logo_problem *p, const logo_bf16
     char *base = (char *)ws;
     uint16_t *qc = (uint16_t *)(base + w.qc);
     float *ndelta = (float *)(base + w.delta);
-    st = hip_status(launch_fill_zero((int64_t)N * H * d, dq, s), s);
-    if (st == LOGO_OK && cap > 0)
-        st = hip_status(launch_sparse_prep(cap, H, d, cu_sel + p->num_seqs, sel_idx, q, o_global,
-                                           dout, qc, ndelta, s),
-                        s);
+    st = hip_status(launch_sparse_prep(cap, H, d, cu_sel + p->num_seqs, sel_idx, q, o_global,
+                                       dout, qc, ndelta, dq, (int64_t)N * H * d, s),
+                    s);
     if (st != LOGO_OK)
         return st;
     BwdArgs a = make_bwd_args(p);

@@ -286,17 +286,29 @@ struct FusionBwdArgs {
 int fusion_bwd_tokens_per_pass(int hq, int head_dim);
 bool fusion_bwd_supported(int hq, int head_dim);
 hipError_t launch_fusion_bwd(const FusionBwdArgs &a, int grid, int head_dim, hipStream_t s);
-hipError_t launch_gate_grad(int n, int hq, const float *side, float *dgate, hipStream_t s);
-// gain-gradient column sums: tmp holds gain_grad_chunks(rows) x cols floats
+// The reductions that follow it (bwd_reduce_kernel); part / tmp / dgain:
+// [0] local, [1] global branch.
+struct BwdReduceArgs {
+    int32_t n, hq, gate_blocks, rows, cols, chunks;
+    const float *side;
+    float *dgate;
+    const float *part[2];
+    float *out[2];                     // NULL: no output for that branch
+    float *zero;
+    int64_t n_zero;
+};
+// gain-gradient column sums: tmp[br] holds gain_grad_chunks(rows) x cols floats
 int gain_grad_chunks(int rows);
-hipError_t launch_gain_grad(int rows, int cols, const float *part, float *tmp, float *out,
-                            hipStream_t s);
-hipError_t launch_fill_zero(int64_t n, float *x, hipStream_t s);
+hipError_t launch_bwd_reduce(int n, int hq, const float *side, float *dgate, int rows, int cols,
+                             const float *const part[2], float *const tmp[2],
+                             float *const dgain[2], float *zero, int64_t n_zero, hipStream_t s);
 // Compact Q rows + -Delta for the standalone query-sparse backward: ranks
-// below min(n_sel_dev[0], cap) (the selected count, read on the device).
+// below min(n_sel_dev[0], cap) (the selected count, read on the device); the
+// same launch clears n_zero floats of `zero`.
 hipError_t launch_sparse_prep(int64_t cap, int hq, int head_dim, const int32_t *n_sel_dev,
                               const int32_t *sel_idx, const uint16_t *q, const float *o,
-                              const uint16_t *dout, uint16_t *qc, float *ndelta, hipStream_t s);
+                              const uint16_t *dout, uint16_t *qc, float *ndelta, float *zero,
+                              int64_t n_zero, hipStream_t s);
 hipError_t launch_attn_delta(int64_t n, int hq, int head_dim, const uint16_t *o,
                              const uint16_t *dout, float *ndelta, hipStream_t s);
 hipError_t launch_bwd_dq(int mode, int head_dim, const BwdArgs &a, int grid, hipStream_t s);
