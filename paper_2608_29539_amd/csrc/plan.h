@@ -35,7 +35,7 @@ template <int E>
 struct PlanLds {
     SparseTile tmp[E], out[E];
     int32_t scratch[2 * E];
-    int32_t hist[kBuckets];
+    alignas(16) int32_t hist[kBuckets];
     int32_t wave_part[16];
     int32_t carry;
     unsigned long long total_blocks;
@@ -158,7 +158,139 @@ __device__ void sort_desc(const SparseTile *src, SparseTile *dst, int n, int max
     __syncthreads();
 }
 
+// Tiles up to which the table is built by build_plan_small.
+constexpr int kSmallPlanTiles = 256;
+
+// The rule of the KV split: entries of a tile of nb blocks (step 4 of
+// build_plan).
+__device__ __forceinline__ long long split_target(unsigned long long total_blocks,
+                                                  const PlanArgs &p) {
+    const unsigned long long work =
+        total_blocks * (unsigned long long)p.n_hg +
+        (unsigned long long)(p.extra_blocks > 0 ? p.extra_blocks : 0);
+    const unsigned long long div = (unsigned long long)kSplitDiv * (unsigned long long)p.grid_wgs;
+    const long long target = (long long)((work + div - 1) / div);
+    return target < kMinSplitBlocks ? kMinSplitBlocks : target;
+}
+__device__ __forceinline__ int split_of(int nb, long long target) {
+    if (nb <= target)
+        return 1;
+    const uint32_t t = (uint32_t)target, ns = ((uint32_t)nb + t - 1) / t;   // target < nb
+    return ns < (uint32_t)kMaxSplit ? (int)ns : kMaxSplit;
+}
+// Entry i of a tile split into ns.
+__device__ __forceinline__ SparseTile split_entry(SparseTile t, int i, int ns, int slot) {
+    const uint32_t nb = t.kb_end + 1;           // (at most 2^25 blocks of 64 keys)
+    t.kb_begin = (int)((uint32_t)i * nb / (uint32_t)ns);
+    t.kb_end = (int)((uint32_t)(i + 1) * nb / (uint32_t)ns) - 1;
+    t.split = i;
+    t.nsplit = ns;
+    t.sid = ns > 1 ? slot : -1;
+    return t;
+}
+
 }  // namespace plan_detail
+
+// The table of at most kSmallPlanTiles tiles (and NT sequences), one thread
+// per tile: a tile's place is counted from the lengths of all tiles in LDS
+// instead of sorted into buckets, twice (split slots go to the longest tiles
+// first, entries are ordered by their own length), with 9 barriers instead of
+// about 50.  What bounds the general build is that chain of barriers and
+// scans by one workgroup (a layer of
+// 1024 tokens, 4 heads, whose local launch ends with it: 36.7 us with it, 34.5
+// with this one).  The entries are the general build's, in an
+// order that differs only within its buckets.  Returns false, with nothing
+// written, for larger tables.
+template <int NT, int E>
+__device__ bool build_plan_small(const int32_t *cu, int B, const PlanArgs &p,
+                                 plan_detail::PlanLds<E> &l) {
+    using namespace plan_detail;
+    static_assert(E >= kSmallPlanTiles && kBuckets >= 2 * kSmallPlanTiles, "LDS of the small plan");
+    const int tid = threadIdx.x;
+    if (B >= NT || B >= 2 * E)
+        return false;
+    // tiles per sequence -> exclusive prefix in l.scratch
+    int own = 0;
+    if (tid < B)
+        own = (min(p.cu_sel[tid + 1], p.cap) - min(p.cu_sel[tid], p.cap) + p.tpw - 1) / p.tpw;
+    const int incl = scan_incl<NT>(own, l.wave_part);
+    if (tid < B)
+        l.scratch[tid] = incl - own;
+    if (tid == NT - 1) {
+        l.carry = incl;
+        l.total_blocks = 0;
+    }
+    __syncthreads();
+    const int n_tiles = l.carry;
+    if (n_tiles > kSmallPlanTiles || n_tiles > NT) {
+        __syncthreads();                         // l is rewritten by the general build
+        return false;
+    }
+    // this thread's tile
+    SparseTile t;
+    int nb = 0;
+    if (tid < n_tiles) {
+        const int b = owner(l.scratch, B, tid);
+        const int s0 = min(p.cu_sel[b], p.cap), s1 = min(p.cu_sel[b + 1], p.cap);
+        t.first = s0 + (tid - l.scratch[b]) * p.tpw;
+        t.nrows = min(p.tpw, s1 - t.first);
+        t.seq = b;
+        t.pos_max = p.sel_idx[t.first + t.nrows - 1] - cu[b];
+        t.kb_begin = 0;
+        t.kb_end = t.pos_max / kBlockN;
+        t.split = 0;
+        t.nsplit = 1;
+        t.sid = -1;
+        t.pad[0] = t.pad[1] = t.pad[2] = 0;
+        nb = t.kb_end + 1;
+        atomicAdd(&l.total_blocks, (unsigned long long)nb);
+    }
+    __syncthreads();
+    // split slots, longest tiles first
+    const int want = tid < n_tiles ? split_of(nb, split_target(l.total_blocks, p)) : 1;
+    int32_t *len = l.hist, *cnt = l.hist + kSmallPlanTiles;
+    // sum of cnt over the tiles that come before this thread's of length v
+    // (four tiles per LDS read; past the last one cnt is 0)
+    auto before = [&](int v) {
+        int sum = 0;
+#pragma unroll 4
+        for (int u = 0; u < n_tiles; u += 4) {
+            const i32x4 ln = *reinterpret_cast<const i32x4 *>(len + u);
+            const i32x4 cn = *reinterpret_cast<const i32x4 *>(cnt + u);
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                sum += ln[e] > v || (ln[e] == v && u + e < tid) ? cn[e] : 0;
+        }
+        return sum;
+    };
+    auto publish = [&](int v, int c) {
+        if (tid < n_tiles + 3 && tid < kSmallPlanTiles) {
+            len[tid] = tid < n_tiles ? v : 0;
+            cnt[tid] = tid < n_tiles ? c : 0;
+        }
+        __syncthreads();
+    };
+    publish(nb, want > 1 ? want : 0);
+    const int slot = tid < n_tiles && want > 1 ? before(nb) : 0;
+    const int ns = want > 1 && slot + want <= p.split_slots ? want : 1;
+    __syncthreads();
+    // entries by their own length
+    const int el = (nb + ns - 1) / ns;
+    publish(el, ns);
+    if (tid < n_tiles) {
+        const int at = before(el);
+        for (int i = 0; i < ns; i++)
+            store_tile(p.out + at + i, split_entry(t, i, ns, slot));
+    }
+    const int n_entries = scan_incl<NT>(tid < n_tiles ? ns : 0, l.wave_part);
+    for (int i = tid; i < p.split_slots * p.n_hg; i += NT)
+        p.split_cnt[i] = 0;
+    if (tid < kQueues)
+        p.queue[1 + tid] = 0;
+    if (tid == NT - 1)
+        p.queue[0] = n_entries;
+    return true;
+}
 
 // Build the work table (see the file comment).  cu: device cu_seqlens [B+1].
 template <int NT, int E>
@@ -174,6 +306,8 @@ __device__ void build_plan(const int32_t *cu, int B, const PlanArgs &p,
     int32_t *sa = in_lds ? l.scratch : p.scratch;
     int32_t *sb = sa + (in_lds ? E : stride);
     const int tid = threadIdx.x;
+    if (build_plan_small<NT, E>(cu, B, p, l))
+        return;
 
     // 1. tiles per sequence -> exclusive prefix
     for (int b = tid; b < B; b += NT) {
@@ -220,19 +354,8 @@ __device__ void build_plan(const int32_t *cu, int B, const PlanArgs &p,
     //    the mean load of one persistent workgroup, other work of the grid
     //    included) becomes ns = ceil(blocks / target) entries (at most
     //    kMaxSplit), while partial slots last.
-    const unsigned long long work = l.total_blocks * (unsigned long long)n_hg +
-                                    (unsigned long long)(p.extra_blocks > 0 ? p.extra_blocks : 0);
-    const unsigned long long div = (unsigned long long)kSplitDiv * (unsigned long long)p.grid_wgs;
-    long long target = (long long)((work + div - 1) / div);
-    if (target < kMinSplitBlocks)
-        target = kMinSplitBlocks;
-    auto nsplit_of = [&](const SparseTile &t) {
-        const long long nb = blocks_of(t);
-        if (nb <= target)
-            return 1;
-        const long long ns = (nb + target - 1) / target;
-        return (int)(ns < kMaxSplit ? ns : kMaxSplit);
-    };
+    const long long target = split_target(l.total_blocks, p);
+    auto nsplit_of = [&](const SparseTile &t) { return split_of(blocks_of(t), target); };
     for (int u = tid; u < n_tiles; u += NT) {
         const int ns = nsplit_of(load_tile(out + u));
         sa[u] = ns > 1 ? ns : 0;
@@ -252,17 +375,9 @@ __device__ void build_plan(const int32_t *cu, int B, const PlanArgs &p,
         SparseTile t = load_tile(out + u);
         const int ns = t.pad[0];
         t.pad[0] = 0;
-        const int nb = t.kb_end + 1;
         const int e0 = sb[u];
-        for (int s = 0; s < ns; s++) {
-            SparseTile h = t;
-            h.kb_begin = (int)(((long long)s * nb) / ns);
-            h.kb_end = (int)(((long long)(s + 1) * nb) / ns) - 1;
-            h.split = s;
-            h.nsplit = ns;
-            h.sid = ns > 1 ? sa[u] : -1;
-            store_tile(tmp + e0 + s, h);
-        }
+        for (int s = 0; s < ns; s++)
+            store_tile(tmp + e0 + s, split_entry(t, s, ns, sa[u]));
     }
     __syncthreads();
     // 5. entries longest first

@@ -687,3 +687,33 @@ def test_layer_threshold_overflow(pk, fwd_launches):
     st = err_stats(torch_bf16_to_f64(out), ref["out"])
     report("thr-overflow", st)
     assert st["max_abs"] <= MAX_ABS and st["mean_abs"] <= MEAN_ABS
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [
+    # tiles of 64 rows (G = 4) and 128 rows (G = 1): the table built by one
+    # thread per tile ends at 256 tiles and at a workgroup's number of
+    # sequences
+    ((16384,), 4, 1, 64), ((16385,), 4, 1, 64), ((3000, 13300, 84), 4, 1, 64),
+    ((1,) * 255, 2, 2, 64), ((70,) * 256, 4, 1, 64), ((3,) * 1100, 2, 2, 64), ((129,), 8, 8, 128),
+    ((8192, 1, 0, 500), 1, 1, 128),
+])
+def test_work_table_sizes(pk, lens, hq, hkv, d):
+    """The query-sparse operator with every row selected against the dense
+    kernel, where the work table's build changes: one bf16 rounding of the
+    dense output plus the two kernels' roundings of P."""
+    import torch
+    w = synth.small_workload(lens, hq, hkv, d, 64, 1.0, seed=7100 + len(lens))
+    dev = to_device(synth.make_inputs(w))
+    cu = dev["cu_seqlens"]
+    prob = pk.Problem(cu, hq, hkv, d, 64, cu_seqlens_host=cu.cpu().numpy())
+    N = w.total_tokens
+    sel_idx, cu_sel, _, _ = pk.logo_select(prob, dev["gate"], ratio=1.0)
+    o = pk.logo_global_attn_sparse_q(prob, dev["q"], dev["k"], dev["v"], sel_idx, cu_sel, N)
+    ref = pk.logo_dense_causal_attn(prob, dev["q"], dev["k"], dev["v"])
+    torch.cuda.synchronize()
+    assert int(cu_sel.cpu()[-1]) == N
+    ref = ref.float()
+    rms = ref.pow(2).mean(dim=-1, keepdim=True).sqrt()
+    err = ((o[:N] - ref).abs() / rms).max().item()
+    print(f"[table {len(lens)} seqs N={N} {hq}/{hkv} d={d}] max err / row rms {err:.3g}")
+    assert err <= 4e-2
