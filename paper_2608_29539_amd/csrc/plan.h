@@ -196,11 +196,10 @@ __device__ __forceinline__ SparseTile split_entry(SparseTile t, int i, int ns, i
 // instead of sorted into buckets, twice (split slots go to the longest tiles
 // first, entries are ordered by their own length), with 9 barriers instead of
 // about 50.  What bounds the general build is that chain of barriers and
-// scans by one workgroup (a layer of
-// 1024 tokens, 4 heads, whose local launch ends with it: 36.7 us with it, 34.5
-// with this one).  The entries are the general build's, in an
-// order that differs only within its buckets.  Returns false, with nothing
-// written, for larger tables.
+// scans by one workgroup (a layer of 1024 tokens, 4 heads, whose local launch
+// ends with it: 36.7 us with it, 34.5 with this one).  The entries are the
+// general build's, in an order that differs only within its buckets.  Returns
+// false, with nothing written, for larger tables.
 template <int NT, int E>
 __device__ bool build_plan_small(const int32_t *cu, int B, const PlanArgs &p,
                                  plan_detail::PlanLds<E> &l) {

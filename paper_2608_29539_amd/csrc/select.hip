@@ -36,8 +36,7 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kKeysPerThread = 32;                      // gates per thread per chunk
-constexpr int kSelChunk = kKeysPerThread * kSelThreads;  // tokens per chunk (32768)
+constexpr int kMaxKeysPerThread = 32;                   // gates per thread per chunk
 constexpr int kPartUnit = 4 * kSelThreads;              // smallest part (4096 tokens)
 constexpr int kMaxParts = 16;                           // parts per sequence while parts fit a chunk
 // Word 3 of a raw (untyped, stride 0) buffer descriptor.
@@ -141,7 +140,7 @@ __device__ void permute_lp_head(const LpPrep &p, int head) {
 // Selection, one 1024-thread workgroup per (part, sequence): blockIdx.y is
 // the sequence, blockIdx.x the part, and part p writes the tokens
 // [p * part_tokens, (p + 1) * part_tokens) of the sequence.  part_tokens is
-// 4096 times a power of two up to kSelChunk, or a multiple of kSelChunk, so
+// 4096 times a power of two up to the chunk, or a multiple of the chunk, so
 // a part never straddles two chunks.
 //
 // kThreshold: find thr[b] (ratio mode, every part of the sequence finds the
@@ -151,7 +150,7 @@ __device__ void permute_lp_head(const LpPrep &p, int head) {
 // part); otherwise (one part per sequence) write the sequence's count to
 // cnt[b].
 //
-// The gates of one chunk of kSelChunk tokens stay in registers: slot j of
+// The gates of one chunk of 1024 kKeysPerThread tokens stay in registers: slot j of
 // thread tid holds token c0 + 1024 j + tid, so the lanes of wave w hold the
 // 64 consecutive tokens of block 16 j + w of the chunk.  Slots past the
 // chunk's end hold -inf, which is never selected (gate > thr is false for
@@ -172,12 +171,13 @@ __device__ void permute_lp_head(const LpPrep &p, int head) {
 // ballot per slot gives each block's selected count (kept in LDS), one scan
 // of the 512 block counts gives each block's first rank, and a token's rank
 // adds the selected lanes below it (mbcnt).
-template <bool kThreshold, bool kWrite>
+template <bool kThreshold, bool kWrite, int kKeysPerThread>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int32_t *__restrict__ cu, int B, const float *__restrict__ gate, int mode, float fixed,
     double ratio, float *__restrict__ thr, int32_t *__restrict__ cnt, int32_t *__restrict__ sel_idx,
     int32_t cap, int32_t *__restrict__ cu_sel, int32_t *__restrict__ tok2sel, int part_tokens, int parts,
     int32_t *__restrict__ zero_words, int n_zero, const LpPrep lp) {
+    constexpr int kSelChunk = kKeysPerThread * kSelThreads;   // tokens per chunk
     __shared__ int hist[kProbBins];           // histogram, then the block counts
     __shared__ int s_wave[kSelWaves];
     __shared__ uint32_t s_u[2 * kSelWaves];
@@ -523,6 +523,42 @@ __global__ void budget_kernel(const int32_t *cu_sel, int B, int N, double rho, f
         *realized = (float)f;
 }
 
+template <int KPT>
+hipError_t launch_select_k(const int32_t *cu_seqlens, int num_seqs, int max_seqlen,
+                           const float *gate, int mode, float threshold, double ratio,
+                           int32_t *sel_idx, int32_t sel_capacity, int32_t *cu_sel,
+                           int32_t *tok2sel, float *thr, int32_t *seq_counts, hipStream_t s,
+                           int32_t *zero_words, int n_zero, const LpPrep &lp) {
+    // parts of 4096 * 2^i tokens, at most kMaxParts per sequence unless a
+    // part would exceed one chunk (then one part per chunk)
+    constexpr int kSelChunk = KPT * kSelThreads;
+    int part_tokens = kPartUnit;
+    while (part_tokens < kSelChunk &&
+           ((long long)max_seqlen + part_tokens - 1) / part_tokens > kMaxParts)
+        part_tokens *= 2;
+    const int parts = (int)std::max(1LL, ((long long)max_seqlen + part_tokens - 1) / part_tokens);
+    const int lp_cols = (lp.heads + num_seqs - 1) / num_seqs;   // grid columns of the LP copies
+    if (num_seqs == 1) {
+        hipLaunchKernelGGL((select_kernel<true, true, KPT>), dim3(parts + lp_cols, 1),
+                           dim3(kSelThreads), 0, s, cu_seqlens, 1, gate, mode, threshold, ratio,
+                           thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens,
+                           parts, zero_words, n_zero, lp);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((select_kernel<true, false, KPT>), dim3(1, num_seqs), dim3(kSelThreads), 0,
+                       s, cu_seqlens, num_seqs, gate, mode, threshold, ratio, thr, seq_counts,
+                       sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens, 1, nullptr, 0,
+                       LpPrep{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((select_kernel<false, true, KPT>), dim3(parts + lp_cols, num_seqs),
+                       dim3(kSelThreads), 0, s, cu_seqlens, num_seqs, gate, mode, threshold,
+                       ratio, thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel,
+                       part_tokens, parts, zero_words, n_zero, lp);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_budget_update(const int32_t *cu_sel, int num_seqs, int n_tokens, double rho,
@@ -537,33 +573,17 @@ hipError_t launch_select(const int32_t *cu_seqlens, int num_seqs, int max_seqlen
                          int32_t *sel_idx, int32_t sel_capacity, int32_t *cu_sel,
                          int32_t *tok2sel, float *thr, int32_t *seq_counts, hipStream_t s,
                          int32_t *zero_words, int n_zero, const LpPrep &lp) {
-    // parts of 4096 * 2^i tokens, at most kMaxParts per sequence unless a
-    // part would exceed one chunk (then one part per chunk)
-    int part_tokens = kPartUnit;
-    while (part_tokens < kSelChunk &&
-           ((long long)max_seqlen + part_tokens - 1) / part_tokens > kMaxParts)
-        part_tokens *= 2;
-    const int parts = (int)std::max(1LL, ((long long)max_seqlen + part_tokens - 1) / part_tokens);
-    const int lp_cols = (lp.heads + num_seqs - 1) / num_seqs;   // grid columns of the LP copies
-    if (num_seqs == 1) {
-        hipLaunchKernelGGL((select_kernel<true, true>), dim3(parts + lp_cols, 1),
-                           dim3(kSelThreads), 0, s, cu_seqlens, 1, gate, mode, threshold, ratio,
-                           thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens,
-                           parts, zero_words, n_zero, lp);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((select_kernel<true, false>), dim3(1, num_seqs), dim3(kSelThreads), 0, s,
-                       cu_seqlens, num_seqs, gate, mode, threshold, ratio, thr, seq_counts,
-                       sel_idx, sel_capacity, cu_sel, tok2sel, part_tokens, 1, nullptr, 0,
-                       LpPrep{});
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL((select_kernel<false, true>), dim3(parts + lp_cols, num_seqs),
-                       dim3(kSelThreads), 0, s, cu_seqlens, num_seqs, gate, mode, threshold,
-                       ratio, thr, seq_counts, sel_idx, sel_capacity, cu_sel, tok2sel,
-                       part_tokens, parts, zero_words, n_zero, lp);
-    return hipGetLastError();
+    // Gates per thread: 4, 8, 16 or 32, the fewest that hold the longest
+    // sequence in one chunk (32 also where none does).  Every pass is unrolled
+    // over them, and a wave steps over the slots it does not use one by one:
+    // with 32 slots a sequence of 1024 tokens took 10.3 us and takes 5.4 with
+    // 4; 8192 tokens 12.4 and 9.0 (8); 16384 tokens 13.8 and 12.4 (16).
+    const auto launch = max_seqlen <= 4 * kSelThreads    ? launch_select_k<4>
+                        : max_seqlen <= 8 * kSelThreads  ? launch_select_k<8>
+                        : max_seqlen <= 16 * kSelThreads ? launch_select_k<16>
+                                                         : launch_select_k<kMaxKeysPerThread>;
+    return launch(cu_seqlens, num_seqs, max_seqlen, gate, mode, threshold, ratio, sel_idx,
+                  sel_capacity, cu_sel, tok2sel, thr, seq_counts, s, zero_words, n_zero, lp);
 }
 
 hipError_t launch_sparse_plan(const int32_t *cu_seqlens, int num_seqs, const PlanArgs &plan,

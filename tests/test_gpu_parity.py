@@ -717,3 +717,21 @@ def test_work_table_sizes(pk, lens, hq, hkv, d):
     err = ((o[:N] - ref).abs() / rms).max().item()
     print(f"[table {len(lens)} seqs N={N} {hq}/{hkv} d={d}] max err / row rms {err:.3g}")
     assert err <= 4e-2
+
+
+@pytest.mark.parametrize("T", [1, 1023, 1024, 1025, 4095, 4096, 4097, 8192, 8193, 16384, 16385,
+                               32768, 32769])
+@pytest.mark.parametrize("kind", ["uniform", "ties", "outside"])
+def test_select_slots_per_thread(pk, T, kind):
+    """The selection at the ends of each number of gates per thread (4, 8, 16,
+    32: 1024 tokens each), one and several sequences, the bin search, tied
+    gates and the radix fallback: bit-exact against the oracle."""
+    for lens in ((T,), (T, 0, max(1, T // 2), 77)):
+        rng = np.random.default_rng(9000 + T)
+        N = sum(lens)
+        gate = (rng.random(N, dtype=np.float32) if kind == "uniform" else
+                (rng.integers(0, 33, N) / 32.0).astype(np.float32) if kind == "ties" else
+                (rng.standard_normal(N) * 3.0).astype(np.float32))
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        for mode, val in (("ratio", 0.3), ("threshold", 0.5)):
+            _select_and_compare(pk, gate, cu, mode, val, f"slots T={T} {kind} {mode}")
