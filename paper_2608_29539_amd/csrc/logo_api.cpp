@@ -625,17 +625,28 @@ logo_status run_global(const logo_problem *p, const logo_bf16 *q, const logo_bf1
 }
 
 // logo_attn_fwd's launches: both branches in one launch (layer_kernel) when
-// their workgroups have the same waves and the local branch gives each
-// persistent workgroup at least kLayerMinLocalBlocks KV blocks of work --
-// enough to cover the work table, which the launch's first workgroup builds
-// (~15-20 us) while the others run local items; otherwise the local launch,
-// then the global one.  LOGO_FWD_LAUNCHES=1 or 2 picks one or the other where
-// both are possible (tests run both).
-constexpr long long kLayerMinLocalBlocks = 8;
+// their workgroups have the same waves and the local branch gives the
+// persistent workgroups enough work beside the work table, which the launch's
+// first workgroup builds while the others run local items; otherwise the local
+// launch, then the global one.  Where the line lies, in KV blocks of local work
+// per persistent workgroup (us per layer, one launch / two):
+//   8 waves, d = 128: no line.  0.4 blocks 39.8 / 47.2, 1.0 39.5 / 46.2, 3.0
+//     42.7 / 53.2, 10 (2048 tokens, 32 heads) 72.3 / 69.5, 20 99.8 / 108.3
+//   8 waves, d = 64: 1.5 (0.25 blocks 35.0 / 33.7, 0.9 42.4 / 38.2, 1.8 40.6 /
+//     43.2)
+//   4 waves (Hq = Hkv): 8 (2.8 blocks 78.5 / 54.3, 5.5 91.1 / 68.4, 11 103.6 /
+//     108.3): half of the grid starts with local items, and the global ones
+//     wait for the table
+// LOGO_FWD_LAUNCHES=1 or 2 picks one or the other where both are possible
+// (tests run both).
+long long layer_min_half_blocks(int waves, int head_dim) {
+    return waves == 8 ? (head_dim == 128 ? 0 : 3) : 16;
+}
 struct LayerPlan {
     int waves = 0, grid = 0;
     long long items = 0;          // local items (an upper bound; the valid ones a prefix)
     long long extra_blocks = 0;   // their KV blocks, ~(w + tpw) / 64 + 1 each
+    bool enough = false;          // local work for the one-launch plan
 };
 
 logo_status layer_plan(const logo_problem *p, LayerPlan &lp) {
@@ -654,6 +665,7 @@ logo_status layer_plan(const logo_problem *p, LayerPlan &lp) {
     lp.grid = grid;
     lp.items = (long long)tp.n_hg * (tiles + p->num_seqs);
     lp.extra_blocks = (long long)tp.n_hg * tiles * ((span + kBlockN - 1) / kBlockN + 1);
+    lp.enough = 2 * lp.extra_blocks >= layer_min_half_blocks(waves, p->head_dim) * grid;
     return LOGO_OK;
 }
 
@@ -665,7 +677,7 @@ bool use_one_launch(const LayerPlan &lp) {
         return true;
     if (e && e[0] == '2')
         return false;
-    return lp.extra_blocks >= kLayerMinLocalBlocks * lp.grid;
+    return lp.enough;
 }
 
 // The one-launch layer: the local items and the global work table's items in

@@ -735,3 +735,26 @@ def test_select_slots_per_thread(pk, T, kind):
         cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
         for mode, val in (("ratio", 0.3), ("threshold", 0.5)):
             _select_and_compare(pk, gate, cu, mode, val, f"slots T={T} {kind} {mode}")
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,d,win,launches", [
+    ((512,), 8, 2, 128, 256, 1), ((1,), 4, 1, 128, 1, 1), ((1024,), 8, 2, 64, 128, 2),
+    ((1500, 900), 16, 4, 64, 256, 1), ((4096,), 8, 8, 128, 512, 2), ((8192,), 8, 8, 128, 512, 1),
+])
+def test_fwd_launch_rule(pk, monkeypatch, seqlens, hq, hkv, d, win, launches):
+    """Which launch plan a problem gets on either side of each line, and that
+    the layer is within its bar there."""
+    import torch
+    monkeypatch.delenv("LOGO_FWD_LAUNCHES", raising=False)
+    w = synth.small_workload(seqlens, hq, hkv, d, win, 0.25, seed=7300 + sum(seqlens))
+    x = synth.make_inputs(w)
+    dev = to_device(x)
+    prob = problem(pk, x, dev, w)
+    assert pk.logo_attn_fwd_launches(prob) == launches
+    if sum(seqlens) > 3000:
+        return
+    out = pk.logo_attn_fwd(prob, dev["q"], dev["k"], dev["v"], dev["gate"], ratio=0.25)[0]
+    torch.cuda.synchronize()
+    ref = oracle.logo_fwd(x["q"], x["k"], x["v"], x["gate"], x["cu_seqlens"], win, ratio=0.25)
+    st = err_stats(torch_bf16_to_f64(out), ref["out"])
+    assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3, st
