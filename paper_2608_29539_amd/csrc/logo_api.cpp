@@ -630,8 +630,10 @@ logo_status run_global(const logo_problem *p, const logo_bf16 *q, const logo_bf1
 // first workgroup builds while the others run local items; otherwise the local
 // launch, then the global one.  Where the line lies, in KV blocks of local work
 // per persistent workgroup (us per layer, one launch / two):
-//   8 waves, d = 128: no line.  0.4 blocks 39.8 / 47.2, 1.0 39.5 / 46.2, 3.0
-//     42.7 / 53.2, 10 (2048 tokens, 32 heads) 72.3 / 69.5, 20 99.8 / 108.3
+//   8 waves, d = 128: sequences of more than 128 tokens, whatever the blocks
+//     (64 tokens 27.2 / 25.1, 3 of 60-100 tokens 31.7 / 29.9, 130 tokens 28.5 /
+//     29.0, 256 tokens 32.1 / 36.5; 0.4 blocks 39.8 / 47.2, 1.0 39.5 / 46.2, 3.0
+//     42.7 / 53.2, 10 (2048 tokens, 32 heads) 72.3 / 69.5, 20 99.8 / 108.3)
 //   8 waves, d = 64: 1.5 (0.25 blocks 35.0 / 33.7, 0.9 42.4 / 38.2, 1.8 40.6 /
 //     43.2)
 //   4 waves (Hq = Hkv): 8 (2.8 blocks 78.5 / 54.3, 5.5 91.1 / 68.4, 11 103.6 /
@@ -639,8 +641,10 @@ logo_status run_global(const logo_problem *p, const logo_bf16 *q, const logo_bf1
 //     wait for the table
 // LOGO_FWD_LAUNCHES=1 or 2 picks one or the other where both are possible
 // (tests run both).
-long long layer_min_half_blocks(int waves, int head_dim) {
-    return waves == 8 ? (head_dim == 128 ? 0 : 3) : 16;
+bool layer_enough_local_work(const logo_problem *p, int waves, long long blocks, int grid) {
+    if (waves == 8 && p->head_dim == 128)
+        return p->max_seqlen > 128;
+    return 2 * blocks >= (waves == 8 ? 3 : 16) * (long long)grid;
 }
 struct LayerPlan {
     int waves = 0, grid = 0;
@@ -665,7 +669,7 @@ logo_status layer_plan(const logo_problem *p, LayerPlan &lp) {
     lp.grid = grid;
     lp.items = (long long)tp.n_hg * (tiles + p->num_seqs);
     lp.extra_blocks = (long long)tp.n_hg * tiles * ((span + kBlockN - 1) / kBlockN + 1);
-    lp.enough = 2 * lp.extra_blocks >= layer_min_half_blocks(waves, p->head_dim) * grid;
+    lp.enough = layer_enough_local_work(p, waves, lp.extra_blocks, grid);
     return LOGO_OK;
 }
 

@@ -738,7 +738,7 @@ def test_select_slots_per_thread(pk, T, kind):
 
 
 @pytest.mark.parametrize("seqlens,hq,hkv,d,win,launches", [
-    ((512,), 8, 2, 128, 256, 1), ((1,), 4, 1, 128, 1, 1), ((1024,), 8, 2, 64, 128, 2),
+    ((512,), 8, 2, 128, 256, 1), ((129,), 4, 1, 128, 1, 1), ((128, 1), 4, 1, 128, 9, 2), ((1024,), 8, 2, 64, 128, 2),
     ((1500, 900), 16, 4, 64, 256, 1), ((4096,), 8, 8, 128, 512, 2), ((8192,), 8, 8, 128, 512, 1),
 ])
 def test_fwd_launch_rule(pk, monkeypatch, seqlens, hq, hkv, d, win, launches):
