@@ -600,7 +600,7 @@ void bwd_dkv_kernel(const BwdArgs a) {
                     const int qpos = (MODE == kModeGlobal ? __float_as_int(srow[buf][2][qi]) : r0 + qi) - base;
                     bool ok = (qi < nv) & (key <= qpos);
                     if (MODE == kModeLocal)
-                        ok = ok & (qpos < key + w);
+                        ok = ok & (qpos - key < w);  // (w may be the largest int)
                     x = ok ? x : kNegInf;                // P = 0
                 }
                 p[qh][i] = __builtin_amdgcn_exp2f(x);

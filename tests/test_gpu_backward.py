@@ -330,3 +330,25 @@ def test_backward_full_size_sampled(pk, name, n_sel_rows, n_uns_rows, n_keys):
 def test_backward_pipeline_edges(pk, lens, G, d, win, ratio):
     w = synth.small_workload(lens, 2 * G, 2, d, win, ratio, seed=5300 + sum(lens))
     run_case(pk, w, ratio=ratio, distinct=G == 2, tag=f"edges G={G} r={ratio}")
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [
+    ((300, 129), 4, 2, 128), ((200,), 4, 4, 64), ((1, 33, 128), 8, 2, 64),
+])
+def test_window_of_the_largest_int(pk, lens, hq, hkv, d):
+    """Every window of at least the longest sequence is the same problem, up to
+    the largest int: outputs and all gradients bit for bit."""
+    import torch
+    res = []
+    for win in (max(lens), 2**31 - 1):
+        w = synth.small_workload(lens, hq, hkv, d, win, 0.25, seed=5600 + sum(lens))
+        dev = to_device(dict(synth.make_inputs(w), dout=synth.make_dout(w, 1)))
+        prob = pk.Problem(dev["cu_seqlens"], hq, hkv, d, win,
+                          cu_seqlens_host=dev["cu_seqlens"].cpu().numpy())
+        t = (prob, dev["q"], dev["k"], dev["v"], dev["gate"])
+        st = pk.logo_attn_fwd_train(*t, ratio=0.25)
+        res.append(dict(out=st["out"], lse_local=st["lse_local"],
+                        **pk.logo_attn_bwd(*t, st, dev["dout"])))
+    torch.cuda.synchronize()
+    for n in res[0]:
+        assert torch.equal(res[0][n], res[1][n]), n
