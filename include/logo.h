@@ -411,7 +411,11 @@ logo_status logo_dense_causal_attn_bwd(const logo_problem *p, const logo_bf16 *q
  *              in its first n_active entries.
  *   n_active   device int32 or NULL: the number of selected sequences.
  *   ws         >= logo_workspace_bytes(p, LOGO_ENTRY_DECODE, 0) bytes,
- *              256-byte aligned (partial results of the key chunks).
+ *              256-byte aligned (partial results of the key chunks).  A small
+ *              step's short chunks need more than a longer cache's step; a
+ *              workspace of the size given for any longer max_seqlen up to
+ *              65536 (the rest of p the same) is taken too: the keys then go
+ *              in longer chunks, whose sums round differently in fp32.
  * Asynchronous on `stream`; nothing is enqueued on error.
  */
 logo_status logo_decode(const logo_problem *p, const logo_bf16 *q, const logo_bf16 *k,

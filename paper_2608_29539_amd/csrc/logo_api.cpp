@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -261,37 +262,19 @@ struct DecodePlan {
     long long n_local_items, n_global_items;
     size_t act, rank_of, n_act, part_local, part_global, total;
 };
-DecodePlan decode_plan(const logo_problem *p) {
+
+// The plan with chunks of kc keys.
+DecodePlan decode_plan_of(const logo_problem *p, int kc) {
     DecodePlan d;
     const long long maxL = p->max_seqlen > 0 ? p->max_seqlen : 1;
-    // Keys per chunk: 512 or more (a workgroup's fixed cost -- query loads,
-    // stream and wave merges, the partial's store -- is then small next to
-    // its 256 KiB of K / V per KV head at d = 128), at most 128 chunks per
-    // cache, a multiple of 32.
-    long long kc = (maxL + 127) / 128;
-    kc = ((kc + 31) / 32) * 32;
-    d.kc = (int)(kc < 512 ? 512 : kc);
+    d.kc = kc;
     const int g = p->num_q_heads / p->num_kv_heads;
     d.gh = g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1);
     d.nhg = g / d.gh;
     const long long wl = maxL < p->window ? maxL : p->window;
-    d.chunks_local = (int)((wl + d.kc - 1) / d.kc);
-    d.chunks_global = (int)((maxL + d.kc - 1) / d.kc);
+    d.chunks_local = (int)((wl + kc - 1) / kc);
+    d.chunks_global = (int)((maxL + kc - 1) / kc);
     const long long per_row = (long long)p->num_kv_heads * d.nhg;
-    // Few caches: shorter chunks while the step has fewer than 1024 work
-    // items (four workgroups per CU) and a cache at most 32 chunks, since
-    // then a workgroup's serial walk over its keys sets the time.  One cache
-    // of 4K tokens, 32 / 8 heads: 22.6 -> 15.8 us per step with 128-key
-    // chunks (64: 18.1); four of 8K tokens, 8 heads: 27.4 -> 25.3.  Past
-    // that: 16 caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with
-    // shorter ones, one cache of 32K tokens 36.3 with 512 and 44.9 with 256.
-    // (The partial results of such a step stay under 5 MB.)
-    while (d.kc > 128 && (maxL + d.kc / 2 - 1) / (d.kc / 2) <= 32 &&
-           p->num_seqs * per_row * (d.chunks_local + d.chunks_global) < 1024) {
-        d.kc /= 2;
-        d.chunks_local = (int)((wl + d.kc - 1) / d.kc);
-        d.chunks_global = (int)((maxL + d.kc - 1) / d.kc);
-    }
     d.n_local_items = (long long)p->num_seqs * per_row * d.chunks_local;
     d.n_global_items = (long long)p->num_seqs * per_row * d.chunks_global;
     const size_t slot = sizeof(float) * (size_t)d.gh * (p->head_dim + 2);
@@ -307,6 +290,36 @@ DecodePlan decode_plan(const logo_problem *p) {
     d.part_global = off;
     off += align_up(slot * (size_t)d.n_global_items);
     d.total = off;
+    return d;
+}
+
+// room: the workspace at hand.  The shorter chunks of a small step need more
+// of it than a longer cache's step does (one cache, 32 / 8 heads, d = 128: 4096
+// tokens 666 KB, 8193 tokens 317 KB), so they are taken only as far as they
+// fit: a workspace for a longer context serves every shorter one.
+DecodePlan decode_plan(const logo_problem *p, size_t room) {
+    const long long maxL = p->max_seqlen > 0 ? p->max_seqlen : 1;
+    // Keys per chunk: 512 or more (a workgroup's fixed cost -- query loads,
+    // stream and wave merges, the partial's store -- is then small next to
+    // its 256 KiB of K / V per KV head at d = 128), at most 128 chunks per
+    // cache, a multiple of 32.
+    long long kc = (maxL + 127) / 128;
+    kc = ((kc + 31) / 32) * 32;
+    DecodePlan d = decode_plan_of(p, (int)(kc < 512 ? 512 : kc));
+    // Few caches: shorter chunks while the step has fewer than 1024 work
+    // items (four workgroups per CU) and a cache at most 32 chunks, since
+    // then a workgroup's serial walk over its keys sets the time.  One cache
+    // of 4K tokens, 32 / 8 heads: 22.6 -> 15.8 us per step with 128-key
+    // chunks (64: 18.1); four of 8K tokens, 8 heads: 27.4 -> 25.3.  Past
+    // that: 16 caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with
+    // shorter ones, one cache of 32K tokens 36.3 with 512 and 44.9 with 256.
+    while (d.kc > 128 && (maxL + d.kc / 2 - 1) / (d.kc / 2) <= 32 &&
+           d.n_local_items + d.n_global_items < 1024) {
+        const DecodePlan half = decode_plan_of(p, d.kc / 2);
+        if (half.total > room)
+            break;
+        d = half;
+    }
     return d;
 }
 
@@ -901,7 +914,7 @@ size_t logo_workspace_bytes(const logo_problem *p, int entry, int32_t sel_capaci
     case LOGO_ENTRY_GLOBAL: return global_ws(p, cap).total;
     case LOGO_ENTRY_FWD: return fwd_ws(p, cap).total;
     case LOGO_ENTRY_FWD_QPHI: return fwd_ws(p, cap, true).total;
-    case LOGO_ENTRY_DECODE: return decode_plan(p).total;
+    case LOGO_ENTRY_DECODE: return decode_plan(p, SIZE_MAX).total;
     case LOGO_ENTRY_FWD_TRAIN: return fwd_ws(p, cap).total;
     case LOGO_ENTRY_BWD: return bwd_ws(p, cap).total;
     case LOGO_ENTRY_DENSE_BWD: return dense_bwd_ws(p);
@@ -1096,15 +1109,16 @@ logo_status decode_run(const logo_problem *p, const logo_bf16 *q, const logo_bf1
                 return LOGO_ERR_SHAPE;
     if ((long long)p->num_seqs * p->num_q_heads >= (1LL << 31))
         return LOGO_ERR_UNSUPPORTED;
-    const DecodePlan d = decode_plan(p);
+    if (noalloc)
+        ws_bytes = (size_t)LOGO_NOALLOC_SCRATCH_BYTES;
+    const DecodePlan d = decode_plan(p, ws_bytes);
     if (d.n_local_items + d.n_global_items >= (1LL << 31))
         return LOGO_ERR_UNSUPPORTED;
     if (noalloc) {
-        if (d.total > (size_t)LOGO_NOALLOC_SCRATCH_BYTES)
+        if (d.total > ws_bytes)
             return LOGO_ERR_SCRATCH_LIMIT;
         if ((st = device_scratch(&ws)) != LOGO_OK)
             return st;
-        ws_bytes = (size_t)LOGO_NOALLOC_SCRATCH_BYTES;
     }
     st = check_ws(ws, ws_bytes, d.total);
     if (st != LOGO_OK)

@@ -177,3 +177,34 @@ def test_decode_chunk_rules(pk, lens, hq, hkv, d, win):
     w = synth.small_workload(lens, hq, hkv, d, win, 0.0, seed=3300 + sum(lens))
     for thr in (-math.inf, 0.5):
         run_case(pk, w, thr, gains=True, tag=f"chunks {lens[0]} thr={thr}")
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,win,longer", [
+    # the shorter chunks of these steps need more workspace than the steps of
+    # the longer caches: 512-key chunks fit, or 256-key ones but not 128
+    ((4096,), 32, 8, 128, 1024, 8193), ((2048, 700), 8, 2, 64, 300, 8193),
+    ((4096,), 32, 8, 128, 1024, 16384), ((4000,), 4, 4, 128, 64, 8193),
+])
+def test_decode_workspace_of_a_longer_cache(pk, lens, hq, hkv, d, win, longer):
+    """A workspace sized for a longer context serves every shorter one."""
+    import torch
+    w = synth.small_workload(lens, hq, hkv, d, win, 0.0, seed=3500 + sum(lens))
+    x = synth.make_decode_inputs(w)
+    dev = to_device(x)
+    kw = dict(total_tokens=w.total_tokens)
+    prob = pk.Problem(dev["cu_seqlens"], hq, hkv, d, win, max_seqlen=max(lens), **kw)
+    long = pk.Problem(dev["cu_seqlens"], hq, hkv, d, win, max_seqlen=longer, **kw)
+    need = pk.logo_workspace_bytes(long, pk.LOGO_ENTRY_DECODE)
+    assert need < pk.logo_workspace_bytes(prob, pk.LOGO_ENTRY_DECODE)
+    ref = oracle.decode(x["q"], x["k"], x["v"], x["gate"], x["cu_seqlens"], win, 0.2)
+    # past the workspace's end the step must not write
+    for bytes_ in (need, pk.logo_workspace_bytes(prob, pk.LOGO_ENTRY_DECODE)):
+        room = torch.full((bytes_ + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = pk.logo_decode(prob, dev["q"], dev["k"], dev["v"], dev["gate"], threshold=0.2,
+                             ws=room[:bytes_])[0]
+        torch.cuda.synchronize()
+        assert bool((room[bytes_:] == 0xA5).all()), bytes_
+        st = err_stats(torch_bf16_to_f64(out), ref["out"])
+        print(f"[decode ws {lens} {bytes_} B] " + " ".join(f"{k}={v:.3g}" for k, v in st.items()),
+              flush=True)
+        assert st["max_abs"] <= MAX_ABS and st["mean_abs"] <= MEAN_ABS, (bytes_, st)
