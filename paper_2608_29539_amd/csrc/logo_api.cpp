@@ -305,7 +305,7 @@ DecodePlan decode_plan(const logo_problem *p, size_t room) {
     // cache, a multiple of 32.
     long long kc = (maxL + 127) / 128;
     kc = ((kc + 31) / 32) * 32;
-    DecodePlan d = decode_plan_of(p, (int)(kc < 512 ? 512 : kc));
+    DecodePlan d = decode_plan_of(p, (int)(kc < 512 ? 512 : kc)), half = d;
     // Few caches: shorter chunks while the step has fewer than 1024 work
     // items (four workgroups per CU) and a cache at most 32 chunks, since
     // then a workgroup's serial walk over its keys sets the time.  One cache
@@ -313,12 +313,23 @@ DecodePlan decode_plan(const logo_problem *p, size_t room) {
     // chunks (64: 18.1); four of 8K tokens, 8 heads: 27.4 -> 25.3.  Past
     // that: 16 caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with
     // shorter ones, one cache of 32K tokens 36.3 with 512 and 44.9 with 256.
-    while (d.kc > 128 && (maxL + d.kc / 2 - 1) / (d.kc / 2) <= 32 &&
-           d.n_local_items + d.n_global_items < 1024) {
-        const DecodePlan half = decode_plan_of(p, d.kc / 2);
+    // (With every cache selected, twice the items of a well filled step cost
+    // more than the shorter walk gives: 16 of 1024 tokens, 32 / 8 heads, 27.3
+    // -> 28.4 us then, 21.4 -> 14.3 with none selected, which the host cannot
+    // tell apart.)
+    // Above 512 work items (two workgroups per CU), chunks of more than half
+    // of the longest cache are left out: the walk is then hardly shorter and
+    // every cache makes a second item (32 caches of 300 tokens, 32 / 8 heads:
+    // 21.3 us with one chunk, 26.6 with 256 keys; 100 of 150 tokens, 8 / 4
+    // heads: 15.2, 19.0 with 128).  Up to 512: 16 of 200 tokens, 32 / 8 heads,
+    // 12.8 with one chunk, 11.2 with 128 keys.
+    while (half.kc > 128 && (maxL + half.kc / 2 - 1) / (half.kc / 2) <= 32 &&
+           half.n_local_items + half.n_global_items < 1024) {
+        half = decode_plan_of(p, half.kc / 2);
         if (half.total > room)
             break;
-        d = half;
+        if (maxL >= 2 * half.kc || half.n_local_items + half.n_global_items <= 512)
+            d = half;
     }
     return d;
 }

@@ -171,7 +171,10 @@ def test_decode_deterministic(pk):
     ((127, 128, 129), 3, 1, 128, 128), ((2048,), 4, 4, 64, 100), ((2049, 5), 8, 2, 128, 2000),
     ((4096, 4095), 4, 2, 64, 4096), ((4097,), 4, 4, 128, 300), ((8193, 1), 8, 8, 128, 600),
     ((16385,), 4, 1, 64, 16385), ((40000, 130), 2, 1, 128, 129),
-    ((300,) * 40, 16, 8, 64, 200),            # too many items for shorter chunks
+    ((300,) * 40, 16, 8, 64, 200),            # 128 keys: 256 are most of a cache
+    ((300,) * 40, 32, 8, 64, 512),            # 512: 256 make too many items for 128
+    ((300,) * 64, 16, 8, 64, 200),            # too many items for shorter chunks
+    ((600,) * 16, 16, 16, 64, 200),           # too many from 256 keys on
 ])
 def test_decode_chunk_rules(pk, lens, hq, hkv, d, win):
     w = synth.small_workload(lens, hq, hkv, d, win, 0.0, seed=3300 + sum(lens))
