@@ -569,9 +569,9 @@ size_t logo_workspace_bytes(const logo_problem *p, int entry, int32_t sel_capaci
  * logo_attn_fwd_launches -- how logo_attn_fwd (and logo_attn_fwd_qphi /
  * _profiled) runs the two attention branches of problem p when the
  * selection capacity is nonzero: 1 = one persistent launch for both
- * (Hq / Hkv a multiple of 4, or 1, and enough local work per workgroup
- * beside building the global work table inside the launch), 2 = the local
- * launch, then the global one.  Host-only (no GPU work; queries the current
+ * (Hq / Hkv a multiple of 4, or 1, and by the local work per workgroup and
+ * the sequences' average length, since the launch builds the global work table
+ * itself), 2 = the local launch, then the global one.  Host-only (no GPU work; queries the current
  * device's CU count once).  The environment variable LOGO_FWD_LAUNCHES=1 or 2
  * forces one or the other where both are possible.  Returns -1 for an
  * invalid problem or a HIP error.

@@ -649,32 +649,50 @@ logo_status run_global(const logo_problem *p, const logo_bf16 *q, const logo_bf1
 }
 
 // logo_attn_fwd's launches: both branches in one launch (layer_kernel) when
-// their workgroups have the same waves and the local branch gives the
-// persistent workgroups enough work beside the work table, which the launch's
-// first workgroup builds while the others run local items; otherwise the local
-// launch, then the global one.  Where the line lies, in KV blocks of local work
-// per persistent workgroup (us per layer, one launch / two):
-//   8 waves, d = 128: sequences of more than 128 tokens, whatever the blocks
-//     (64 tokens 27.2 / 25.1, 3 of 60-100 tokens 31.7 / 29.9, 130 tokens 28.5 /
-//     29.0, 256 tokens 32.1 / 36.5; 0.4 blocks 39.8 / 47.2, 1.0 39.5 / 46.2, 3.0
-//     42.7 / 53.2, 10 (2048 tokens, 32 heads) 72.3 / 69.5, 20 99.8 / 108.3)
-//   8 waves, d = 64: 1.5 (0.25 blocks 35.0 / 33.7, 0.9 42.4 / 38.2, 1.8 40.6 /
-//     43.2)
-//   4 waves (Hq = Hkv): 8 (2.8 blocks 78.5 / 54.3, 5.5 91.1 / 68.4, 11 103.6 /
-//     108.3): half of the grid starts with local items, and the global ones
-//     wait for the table
+// their workgroups have the same waves and the rule below; otherwise the local
+// launch, then the global one.  The one launch saves the second one and the
+// gap before it, but its first workgroup builds the work table while the
+// others run local items, and every workgroup then waits for the table and
+// takes its items from shared counters: with many sequences the table is long
+// and its items short.  us per layer, one launch / two:
+//   4 waves (Hq = Hkv): from 8 KV blocks of local work per workgroup (2.8
+//     blocks 78.5 / 54.3, 5.5 91.1 / 68.4, 11 103.6 / 108.3): half of the grid
+//     starts with local items, and the global ones wait for the table
+//   8 waves, d = 64: from 1.5 blocks (0.25 blocks 35.0 / 33.7, 0.9 42.4 / 38.2,
+//     1.8 40.6 / 43.2)
+//   8 waves, fewer local items than workgroups: sequences of more than 160
+//     tokens on average (32 / 8 heads; 12 of 160: 59.1 / 47.7; 6 of 192: 34.6 /
+//     39.1; 1024 tokens 44.4 / 57.1), at d = 128 and up to 5/8 of the
+//     workgroups more than 100 (2 of 129: 33.5 / 35.1, 8 of 128 32.0 / 35.5, 8
+//     of 64 28.7 / 31.4, 32 of 16 46.2 / 35.4; 16 of 128, all workgroups, 55.9 /
+//     40.6)
+//   8 waves, more local items: more than 384 tokens on average (16 of 256 tokens
+//     76.3 / 55.9, 32 of 384 184.2 / 138.2, 24 of 512 182.7 / 189.8; 512 of 64
+//     tokens 2.5 times), and twice the workgroups of items only with 8 blocks
+//     (4 of 1024 tokens with a window of 16, every token selected: 140.6 / 107.2)
+// The average, since max_seqlen may be one long sequence among short ones, or a
+// loose bound: 512 of 16 tokens with one of 200, 4 heads, 251.6 / 188.1.  With
+// every token selected the one launch loses up to 7% where it is taken.
 // LOGO_FWD_LAUNCHES=1 or 2 picks one or the other where both are possible
 // (tests run both).
-bool layer_enough_local_work(const logo_problem *p, int waves, long long blocks, int grid) {
-    if (waves == 8 && p->head_dim == 128)
-        return p->max_seqlen > 128;
-    return 2 * blocks >= (waves == 8 ? 3 : 16) * (long long)grid;
+bool layer_one_launch(const logo_problem *p, int waves, long long items, long long blocks,
+                      int grid) {
+    if (waves == 4)
+        return blocks >= 8LL * grid;
+    if (p->head_dim == 64 && 2 * blocks < 3LL * grid)
+        return false;
+    auto longer_than = [&](long long tokens) {
+        return p->total_tokens > tokens * p->num_seqs;
+    };
+    if (items < grid)
+        return longer_than(p->head_dim == 128 && 8 * items <= 5LL * grid ? 100 : 160);
+    return longer_than(384) && (blocks >= 8LL * grid || items < 2LL * grid);
 }
 struct LayerPlan {
     int waves = 0, grid = 0;
     long long items = 0;          // local items (an upper bound; the valid ones a prefix)
     long long extra_blocks = 0;   // their KV blocks, ~(w + tpw) / 64 + 1 each
-    bool enough = false;          // local work for the one-launch plan
+    bool one = false;             // the rule picks one launch
 };
 
 logo_status layer_plan(const logo_problem *p, LayerPlan &lp) {
@@ -693,7 +711,7 @@ logo_status layer_plan(const logo_problem *p, LayerPlan &lp) {
     lp.grid = grid;
     lp.items = (long long)tp.n_hg * (tiles + p->num_seqs);
     lp.extra_blocks = (long long)tp.n_hg * tiles * ((span + kBlockN - 1) / kBlockN + 1);
-    lp.enough = layer_enough_local_work(p, waves, lp.extra_blocks, grid);
+    lp.one = layer_one_launch(p, waves, tp.n_hg * tiles, lp.extra_blocks, grid);
     return LOGO_OK;
 }
 
@@ -705,7 +723,7 @@ bool use_one_launch(const LayerPlan &lp) {
         return true;
     if (e && e[0] == '2')
         return false;
-    return lp.enough;
+    return lp.one;
 }
 
 // The one-launch layer: the local items and the global work table's items in

@@ -740,6 +740,13 @@ def test_select_slots_per_thread(pk, T, kind):
 @pytest.mark.parametrize("seqlens,hq,hkv,d,win,launches", [
     ((512,), 8, 2, 128, 256, 1), ((129,), 4, 1, 128, 1, 1), ((128, 1), 4, 1, 128, 9, 2), ((1024,), 8, 2, 64, 128, 2),
     ((1500, 900), 16, 4, 64, 256, 1), ((4096,), 8, 8, 128, 512, 2), ((8192,), 8, 8, 128, 512, 1),
+    # 8 waves by the average length: short sequences beside a long one, few and
+    # many local items (256 workgroups: one of 8 waves on each CU)
+    ((200,) + (16,) * 100, 4, 1, 128, 512, 2), ((300, 40, 40), 4, 1, 128, 64, 1),
+    ((101,) * 3, 8, 2, 128, 64, 1), ((100,) * 3, 8, 2, 128, 64, 2), ((160,) * 12, 32, 8, 128, 64, 2),
+    ((161,) * 10, 32, 8, 128, 64, 1), ((192,) * 6, 32, 8, 64, 128, 1), ((160,) * 6, 32, 8, 64, 128, 2),
+    ((256,) * 8, 32, 8, 128, 64, 2), ((400,) * 7, 32, 8, 128, 16, 1), ((400,) * 12, 32, 8, 128, 16, 2),
+    ((400,) * 12, 32, 8, 128, 400, 1),
 ])
 def test_fwd_launch_rule(pk, monkeypatch, seqlens, hq, hkv, d, win, launches):
     """Which launch plan a problem gets on either side of each line, and that
