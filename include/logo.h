@@ -430,9 +430,8 @@ logo_status logo_decode(const logo_problem *p, const logo_bf16 *q, const logo_bf
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation): the same decoding step with the same arguments and
  * results, minus the workspace.  Its scratch memory (the partial results of
- * the key chunks, and the selected list and count when active / n_active
- * are NULL) is a fixed device array of LOGO_NOALLOC_SCRATCH_BYTES inside the
- * library, which every GPU the library runs on holds from the module's load
+ * the key chunks) is a fixed device array of LOGO_NOALLOC_SCRATCH_BYTES inside
+ * the library, which every GPU the library runs on holds from the module's load
  * until the process ends.  The call allocates and frees nothing; the first
  * call on a device looks up the array's address there once.
  *   Errors: those of logo_decode, and LOGO_ERR_SCRATCH_LIMIT (nothing

@@ -696,10 +696,9 @@ def logo_decode_noalloc(prob: Problem, q, k, v, gate, out, *, threshold: Optiona
                         threshold_device=None, q_g=None, k_g=None, v_g=None, gain_local=None,
                         gain_global=None, eps: float = 1e-6, active=None, n_active=None):
     """``logo_decode`` without a workspace: the library's fixed device scratch
-    array holds the partial results (and the selected list and count when
-    ``active`` / ``n_active`` are None).  ``out`` [B, Hq, d] bf16 must be
-    given; nothing is allocated.  Returns (out, active, n_active), the last
-    two None when not given."""
+    array holds the partial results.  ``out`` [B, Hq, d] bf16 must be given;
+    nothing is allocated.  Returns (out, active, n_active), the last two None
+    when not given."""
     import torch
     N, Hq, Hkv, d, B = (prob.total_tokens, prob.num_q_heads, prob.num_kv_heads, prob.head_dim,
                         prob.num_seqs)

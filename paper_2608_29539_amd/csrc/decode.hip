@@ -18,8 +18,8 @@
 //                         2d-byte row, and each of the 16 streams keeps two
 //                         rows in flight.  Writes the chunk's unnormalised
 //                         (O, m, l) per head.  One extra workgroup writes
-//                         the compacted list of selected sequences, each
-//                         sequence's rank and the count.
+//                         the compacted list of selected sequences and the
+//                         count, where the caller asks for either.
 //   decode_combine_kernel merges the chunks of each (sequence, head) in chunk
 //                         order, applies ContextNorm to each branch and the
 //                         fusion, and rounds once to bf16.
@@ -73,9 +73,9 @@ __device__ __forceinline__ float decode_threshold(const DecodeArgs &a) {
     return a.sel_mode == 2 ? a.thr_dev[0] : a.thr_host;
 }
 
-// The compacted list of selected sequences (ascending), each sequence's rank
-// (-1 if unselected) and the count: one workgroup, ballot + mbcnt ranks and
-// a carry over chunks of kDecThreads sequences.
+// The compacted list of selected sequences (ascending) and the count, each
+// where it is asked for: one workgroup, ballot + mbcnt ranks and a carry over
+// chunks of kDecThreads sequences.
 __device__ void build_active_list(const DecodeArgs &a) {
     __shared__ int s_cnt[kDecThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,16 +96,12 @@ __device__ void build_active_list(const DecodeArgs &a) {
                 before += s_cnt[i];
             total += s_cnt[i];
         }
-        if (b < a.num_seqs) {
-            const int r = before + below;
-            a.rank_of[b] = z ? r : -1;
-            if (z)
-                a.act[r] = b;
-        }
+        if (z && a.act)
+            a.act[before + below] = b;
         carry += total;
         __syncthreads();                         // s_cnt is rewritten by the next chunk
     }
-    if (tid == 0)
+    if (tid == 0 && a.n_act)
         a.n_act[0] = carry;
 }
 
@@ -129,8 +125,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_attn_kernel(const DecodeAr
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int e = lane % kLanesPerRow, sid = tid / kLanesPerRow;
 
-    // work item -> (branch, sequence, kv head, head group, chunk); the last
-    // workgroup builds the list of selected sequences instead
+    // work item -> (branch, sequence, kv head, head group, chunk); the
+    // workgroup past them builds the list of selected sequences instead
     const int per_row = a.hkv * a.nhg;
     int item = blockIdx.x;
     if (item == a.n_local_items + a.n_global_items) {
@@ -462,7 +458,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const DecodeArgs a)
 
 template <int D, int GH>
 hipError_t launch_attn_gh(const DecodeArgs &a, hipStream_t s) {
-    const int grid = a.n_local_items + a.n_global_items + 1;   // + the list builder
+    const int grid = a.n_local_items + a.n_global_items + (a.act || a.n_act);   // + the list builder
     hipLaunchKernelGGL((decode_attn_kernel<D, GH>), dim3(grid), dim3(kDecThreads), 0, s, a);
     return hipGetLastError();
 }

@@ -260,7 +260,7 @@ BwdArgs make_bwd_args(const logo_problem *p) {
 struct DecodePlan {
     int kc, gh, nhg, chunks_local, chunks_global;
     long long n_local_items, n_global_items;
-    size_t act, rank_of, n_act, part_local, part_global, total;
+    size_t part_local, part_global, total;
 };
 
 // The plan with chunks of kc keys.
@@ -279,12 +279,6 @@ DecodePlan decode_plan_of(const logo_problem *p, int kc) {
     d.n_global_items = (long long)p->num_seqs * per_row * d.chunks_global;
     const size_t slot = sizeof(float) * (size_t)d.gh * (p->head_dim + 2);
     size_t off = 0;
-    d.act = off;
-    off += align_up(sizeof(int32_t) * (size_t)p->num_seqs);
-    d.rank_of = off;
-    off += align_up(sizeof(int32_t) * (size_t)p->num_seqs);
-    d.n_act = off;
-    off += align_up(sizeof(int32_t));
     d.part_local = off;
     off += align_up(slot * (size_t)d.n_local_items);
     d.part_global = off;
@@ -1180,9 +1174,8 @@ logo_status decode_run(const logo_problem *p, const logo_bf16 *q, const logo_bf1
     a.chunks_global = d.chunks_global;
     a.n_local_items = (int32_t)d.n_local_items;
     a.n_global_items = (int32_t)d.n_global_items;
-    a.act = active ? active : (int32_t *)(base + d.act);
-    a.rank_of = (int32_t *)(base + d.rank_of);
-    a.n_act = n_active ? n_active : (int32_t *)(base + d.n_act);
+    a.act = active;
+    a.n_act = n_active;
     a.part_local = (float *)(base + d.part_local);
     a.part_global = (float *)(base + d.part_global);
     a.out = out;

@@ -236,7 +236,7 @@ struct DecodeArgs {
     int32_t kc;                      // keys per chunk
     int32_t chunks_local, chunks_global;
     int32_t n_local_items, n_global_items;
-    int32_t *act, *rank_of, *n_act;  // selected sequences (compacted), rank or -1, count
+    int32_t *act, *n_act;            // selected sequences (compacted), count; or NULL
     int32_t sel_mode;                // 0: threshold thr_host, 2: device threshold thr_dev[0]
     float thr_host;
     const float *thr_dev;

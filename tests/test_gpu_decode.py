@@ -211,3 +211,29 @@ def test_decode_workspace_of_a_longer_cache(pk, lens, hq, hkv, d, win, longer):
         print(f"[decode ws {lens} {bytes_} B] " + " ".join(f"{k}={v:.3g}" for k, v in st.items()),
               flush=True)
         assert st["max_abs"] <= MAX_ABS and st["mean_abs"] <= MEAN_ABS, (bytes_, st)
+
+
+@pytest.mark.parametrize("given", [(), ("active",), ("n_active",)])
+def test_decode_lists_not_asked_for(pk, given):
+    """The selected list and its count are written where they are asked for,
+    and the step's output is the same without either."""
+    import torch
+    w = synth.small_workload((50, 700, 3, 129, 400), 8, 2, 128, 64, 0.0, seed=3600)
+    x = synth.make_decode_inputs(w)
+    dev = to_device(x)
+    prob = pk.Problem(dev["cu_seqlens"], 8, 2, 128, 64, cu_seqlens_host=x["cu_seqlens"])
+    t = (prob, dev["q"], dev["k"], dev["v"], dev["gate"])
+    thr = float(np.sort(x["gate"])[1])
+    ref, act, n = pk.logo_decode(*t, threshold=thr)
+    out = torch.zeros_like(ref)
+    kw = {k: torch.full((5,), -7, dtype=torch.int32, device="cuda") for k in given}
+    if "n_active" in kw:
+        kw["n_active"] = kw["n_active"][:1]
+    pk.logo_decode_noalloc(*t, out, threshold=thr, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    assert int(n.cpu()[0]) == 3
+    if "active" in kw:
+        assert kw["active"].cpu().tolist() == act.cpu().tolist()[:3] + [-7, -7]
+    if "n_active" in kw:
+        assert kw["n_active"].cpu().tolist() == [3]
