@@ -36,6 +36,7 @@
 // 4 consecutive rows, 64 contiguous bytes each).
 #include "logo_internal.h"
 #include "attn_common.h"
+#include "bwd_rules.h"
 
 #include <type_traits>
 #include <utility>
@@ -55,7 +56,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 
 constexpr int kBwdWaves = 4;
-constexpr int kTileRows = 64;   // rows of a staged tile (keys or queries)
+static_assert(kBwdWaves * kWaveKeys == kKeysPerWg, "keys of a dK / dV workgroup");
 
 template <int D>
 __device__ __forceinline__ constexpr int swz(int r) {
@@ -396,8 +397,6 @@ void bwd_dq_kernel(const BwdArgs a) {
 // between its own products, the score accumulators in AGPRs (a copy per value
 // read) and the row scalars staged through registers; dK, dV of the selected
 // rows of 32768 tokens: 2430 -> 2080 us, of the local branch: 1300 -> 1083.
-constexpr int kKeysPerWg = kBwdWaves * 32;
-
 template <int D, int MODE>
 __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void bwd_dkv_kernel(const BwdArgs a) {
@@ -462,35 +461,22 @@ void bwd_dkv_kernel(const BwdArgs a) {
         r_end = s1;
     } else {
         r_begin = base + k0;
-        r_end = base + (int)min((long long)T, (long long)k0 + kKeysPerWg - 1 + w);
+        r_end = base + local_row_end(T, k0, w);
     }
     const int nblk = (r_end - r_begin + kTileRows - 1) / kTileRows;
     const int nsteps = nblk * a.group;                       // every head of the KV group
 
     // The 64-row tiles q of a head that this wave computes, qf .. ql, and
-    // among them the ones that need no mask, qa .. qb - 1: every row of such
-    // a tile sees all of the wave's keys.  (The same for every head; the
-    // other waves' tiles are only staged.)
-    int qf = 0, ql = nblk - 1, qa = 0, qb = (r_end - r_begin) / kTileRows;
-    auto row_pos = [&](int r) { return (MODE == kModeGlobal ? uni(a.sel_idx[r]) : r) - base; };
-    if (j0 >= T) {
-        qf = nblk;
-    } else {
-        while (qf < nblk && row_pos(min(r_begin + qf * kTileRows + kTileRows, r_end) - 1) < j0)
-            qf++;
-        qa = qf;
-        while (qa < nblk && row_pos(r_begin + qa * kTileRows) < j0 + 31)
-            qa++;
-        if (MODE == kModeLocal) {
-            const int jmax = min(j0 + 31, T - 1);
-            ql = (int)min((long long)ql, ((long long)jmax + w - 1 - k0) / kTileRows);
-            const long long full = (long long)j0 + w - k0;   // rows from k0 that see key j0
-            qb = (int)min((long long)qb, full / kTileRows);
-        }
-        if (j0 + 31 >= T)
-            qb = 0;
-        qb = max(qa, min(qb, ql + 1));
-    }
+    // among them the ones that need no mask, qa .. qb - 1.  (The same for every
+    // head.)
+    const DkvTiles tiles = dkv_tiles<MODE == kModeLocal>(
+        r_end - r_begin,
+        [&](int i) {
+            const int r = r_begin + i;
+            return (MODE == kModeGlobal ? uni(a.sel_idx[r]) : r) - base;
+        },
+        T, k0, j0, w);
+    const int qf = tiles.first, ql = tiles.last, qa = tiles.full, qb = tiles.full_end;
 
     const int row_bytes = a.hq * D * 2;
     TileDma<D> dma;
@@ -598,9 +584,7 @@ void bwd_dkv_kernel(const BwdArgs a) {
                 if constexpr (decltype(masked)::value) {
                     const int qi = qh * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
                     const int qpos = (MODE == kModeGlobal ? __float_as_int(srow[buf][2][qi]) : r0 + qi) - base;
-                    bool ok = (qi < nv) & (key <= qpos);
-                    if (MODE == kModeLocal)
-                        ok = ok & (qpos - key < w);  // (w may be the largest int)
+                    const bool ok = (qi < nv) & row_sees_key<MODE == kModeLocal>(qpos, key, w);
                     x = ok ? x : kNegInf;                // P = 0
                 }
                 p[qh][i] = __builtin_amdgcn_exp2f(x);

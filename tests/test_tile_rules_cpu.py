@@ -1,9 +1,12 @@
 """Index rules of the kernels that can be checked without a GPU."""
 import ctypes
 import os
+import subprocess
 
 import numpy as np
 import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
@@ -52,34 +55,71 @@ def test_decode_chunks(pk, B, max_seqlen, hq, hkv, d, win, keys):
     assert ws(max_seqlen) - ws(1) == partials(max_seqlen, keys) - partials(1, keys)
 
 
-def test_dkv_tile_ranges():
-    """The ranges of 64-row tiles that a 32-key wave computes (qf .. ql) and of
-    those without a mask (qa .. qb - 1), as bwd_dkv_kernel forms them for the
-    local branch, against the pairs themselves."""
-    for T, w, k0 in [(1, 1, 0), (300, 1, 128), (300, 64, 128), (700, 257, 256), (513, 5000, 384),
-                     (129, 16, 128), (640, 128, 0), (1000, 100, 896)]:
-        r_end = min(T, k0 + 127 + w)
-        nblk = -(-(r_end - k0) // 64)
-        for wave in range(4):
-            j0 = k0 + wave * 32
-            qf, ql, qa, qb = 0, nblk - 1, 0, (r_end - k0) // 64
-            if j0 >= T:
-                continue
-            while qf < nblk and min(k0 + qf * 64 + 64, r_end) - 1 < j0:
-                qf += 1
-            qa = qf
-            while qa < nblk and k0 + qa * 64 < j0 + 31:
-                qa += 1
-            jmax = min(j0 + 31, T - 1)
-            ql = min(ql, (jmax + w - 1 - k0) // 64)
-            qb = min(qb, (j0 + w - k0) // 64)
-            if j0 + 31 >= T:
-                qb = 0
-            qb = max(qa, min(qb, ql + 1))
-            for q in range(nblk):
-                rows = np.arange(k0 + q * 64, min(k0 + q * 64 + 64, r_end))[:, None]
-                keys = np.arange(j0, jmax + 1)[None, :]
-                sees = (keys <= rows) & (rows < keys + w)
-                assert not sees.any() or qf <= q <= ql, (T, w, k0, wave, q)
-                if qa <= q < qb:
-                    assert rows.size == 64 and keys.size == 32 and sees.all(), (T, w, k0, wave, q)
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """The rules of csrc/bwd_rules.h, which bwd_dkv_kernel calls, on the CPU."""
+    so = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared",
+                    "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    "-static-libubsan", "-I", os.path.join(ROOT, "paper_2608_29539_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c", "dkv_tiles.cpp"), "-o", so], check=True)
+    return ctypes.CDLL(so)
+
+
+BIG = 2**31 - 1
+
+
+def _check_tiles(rules, local, pos, T, k0, w):
+    """Every tile of 64 rows against its pairs: the tiles that a wave leaves out
+    have none, those without a mask have all 64 x 32, and the mask of the others
+    is the definition."""
+    pos = np.ascontiguousarray(pos, np.int32)
+    nblk = -(-pos.size // 64)
+    for wave in range(4):
+        j0 = k0 + wave * 32
+        out = (ctypes.c_int * 4)()
+        rules.dkv_tiles(int(local), pos.ctypes.data_as(ctypes.c_void_p), pos.size, T, k0, wave, w,
+                        out)
+        first, last, full, full_end = out
+        keys = np.arange(j0, min(j0 + 32, T), dtype=np.int64)[None, :]
+        for q in range(nblk):
+            rows = pos[q * 64:q * 64 + 64].astype(np.int64)[:, None]
+            sees = (keys <= rows) & ((rows - keys < w) | (not local))
+            tag = (local, T, w, k0, wave, q, list(out))
+            assert not sees.any() or first <= q <= last, tag
+            if first < nblk and full <= q < full_end:
+                assert sees.shape == (64, 32) and sees.all() and first <= q <= last, tag
+        if first < nblk:
+            # (the kernel's loops run from the last tile to the first)
+            assert 0 <= first <= full <= full_end <= last + 1 <= nblk, (local, T, w, k0, wave)
+
+
+@pytest.mark.parametrize("T,w,k0", [
+    (1, 1, 0), (300, 1, 128), (300, 64, 128), (700, 257, 256), (513, 5000, 384), (129, 16, 128),
+    (640, 128, 0), (1000, 100, 896), (1000, BIG, 0), (257, BIG, 256), (200, BIG - 64, 128),
+    (900, 33, 640), (127, 127, 0), (2000, 1000, 128), (700, 127, 128), (2000, 1087, 640),
+])
+def test_dkv_tile_ranges_local(rules, T, w, k0):
+    end = rules.local_row_end(T, k0, w)
+    # the rows past the end see none of the block's keys, the last one does
+    assert end == max(r for r in range(k0, T) if r - min(k0 + 127, T - 1, r) < w) + 1
+    _check_tiles(rules, True, np.arange(k0, end), T, k0, w)
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_dkv_tile_ranges_global(rules, seed):
+    """Selected rows from the block on: none, few, bursts, nearly all."""
+    rng = np.random.default_rng(8800 + seed)
+    T = int(rng.choice([1, 31, 128, 129, 500, 1500, 4000]))
+    k0 = 128 * int(rng.integers(0, -(-T // 128)))
+    p = float(rng.choice([0.0, 0.02, 0.3, 0.9, 1.0]))
+    pos = k0 + np.nonzero(rng.random(T - k0) < p)[0]
+    _check_tiles(rules, False, pos, T, k0, 1)
+
+
+def test_dkv_mask(rules):
+    for w in (1, 2, 63, 1000, BIG):
+        for q, k in [(0, 0), (5, 5), (5, 6), (70, 7), (70, 8), (1000, 0), (BIG, 0), (BIG, 1),
+                     (BIG - 1, BIG), (0, BIG)]:
+            assert rules.row_sees_key(0, q, k, w) == (k <= q), (q, k, w)
+            assert rules.row_sees_key(1, q, k, w) == (k <= q and q - k < w), (q, k, w)
