@@ -758,10 +758,12 @@ def test_fwd_launch_rule(pk, monkeypatch, seqlens, hq, hkv, d, win, launches):
     dev = to_device(x)
     prob = problem(pk, x, dev, w)
     assert pk.logo_attn_fwd_launches(prob) == launches
-    if sum(seqlens) > 3000:
-        return
-    out = pk.logo_attn_fwd(prob, dev["q"], dev["k"], dev["v"], dev["gate"], ratio=0.25)[0]
+    out, _, _, tok2sel, _ = pk.logo_attn_fwd(prob, dev["q"], dev["k"], dev["v"], dev["gate"],
+                                             ratio=0.25)
     torch.cuda.synchronize()
-    ref = oracle.logo_fwd(x["q"], x["k"], x["v"], x["gate"], x["cu_seqlens"], win, ratio=0.25)
-    st = err_stats(torch_bf16_to_f64(out), ref["out"])
+    rows = np.arange(sum(seqlens), dtype=np.int32)
+    if rows.size > 3000:
+        rows = sample_rows(x["cu_seqlens"], tok2sel.cpu().numpy(), 64, 64, seed=w.seed)
+    ref = oracle_layer_rows(x, win, rows, ratio=0.25)
+    st = err_stats(torch_bf16_to_f64(out)[rows], ref["out"])
     assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3, st
