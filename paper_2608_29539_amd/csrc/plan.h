@@ -158,8 +158,14 @@ __device__ void sort_desc(const SparseTile *src, SparseTile *dst, int n, int max
     __syncthreads();
 }
 
-// Tiles up to which the table is built by build_plan_small.
-constexpr int kSmallPlanTiles = 256;
+// Tiles up to which the table is built by build_plan_small, whose counting
+// takes a step of its loops for every four tiles where the general build's
+// barriers and scans do not depend on the tiles (standalone plan + global
+// launch of 8 / 2 heads, d = 64, one sequence, general / small, us: 16 tiles 32.4
+// / 25.2, 48 43.4 / 41.2, 80 78.1 / 79.7, 144 149.8 / 157.3, 240 314.6 / 332.9;
+// many short sequences, whose tiles are not split: 48 tiles 23.4 / 18.3, 112
+// 24.9 / 23.4, 176 31.1 / 32.9, 240 34.4 / 39.7).
+constexpr int kSmallPlanTiles = 64;
 
 // The rule of the KV split: entries of a tile of nb blocks (step 4 of
 // build_plan).

@@ -691,8 +691,9 @@ def test_layer_threshold_overflow(pk, fwd_launches):
 
 @pytest.mark.parametrize("lens,hq,hkv,d", [
     # tiles of 64 rows (G = 4) and 128 rows (G = 1): the table built by one
-    # thread per tile ends at 256 tiles and at a workgroup's number of
-    # sequences
+    # thread per tile ends at 64 tiles and at a workgroup's number of sequences
+    ((4096,), 4, 1, 64), ((4097,), 4, 1, 64), ((500, 3500, 84), 4, 1, 128), ((1,) * 63, 2, 2, 64),
+    ((70,) * 32, 4, 1, 128), ((8192,), 2, 2, 64), ((8193,), 2, 2, 128),
     ((16384,), 4, 1, 64), ((16385,), 4, 1, 64), ((3000, 13300, 84), 4, 1, 64),
     ((1,) * 255, 2, 2, 64), ((70,) * 256, 4, 1, 64), ((3,) * 1100, 2, 2, 64), ((129,), 8, 8, 128),
     ((8192, 1, 0, 500), 1, 1, 128),
