@@ -101,16 +101,6 @@ __device__ __forceinline__ void dma_wait_barrier() {
     __syncthreads();
 }
 
-// gfx950 LDS transpose read of two 8-byte addresses (8 rows apart in the
-// callers' layouts): within each 16-lane group, lane 4b+e receives element e
-// of the 4-element rows addressed by lanes b, b+4, b+8, b+12.
-__device__ __forceinline__ bf16x8 lds_tr_pair(const void *a0, const void *a1) {
-    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a0);
-    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a1);
-    const s16x4 ab[2] = {a, b};
-    return __builtin_bit_cast(bf16x8, ab);
-}
-
 // The same where the kPending newest of this wave's LDS-bound loads may still
 // be in flight (kPending < 16): a bare barrier, whose memory fence would wait
 // for them.  Every LDS read before it has returned its data already (the
@@ -122,6 +112,16 @@ __device__ __forceinline__ void dma_wait_barrier_but() {
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | kPending);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// gfx950 LDS transpose read of two 8-byte addresses (8 rows apart in the
+// callers' layouts): within each 16-lane group, lane 4b+e receives element e
+// of the 4-element rows addressed by lanes b, b+4, b+8, b+12.
+__device__ __forceinline__ bf16x8 lds_tr_pair(const void *a0, const void *a1) {
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a0);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a1);
+    const s16x4 ab[2] = {a, b};
+    return __builtin_bit_cast(bf16x8, ab);
 }
 
 // Two fp32 -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32.

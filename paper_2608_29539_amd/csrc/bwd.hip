@@ -646,9 +646,9 @@ void bwd_dkv_kernel(const BwdArgs a) {
     using F_ = std::false_type;
     // Steps: the tiles from the last to the first, each for every head of the
     // group, so that all key blocks of a KV head walk the same rows at the
-    // same time and find them in L2 (half
-    // of the L2 misses of the ascending order, heads outermost).  Each step stages the tile two
-    // steps ahead, runs `work` on its own and then waits for the next one's.
+    // same time and find them in L2 (half of the L2 misses of the ascending
+    // order with the heads outermost).  Each step stages the tile two steps
+    // ahead, runs `work` on its own and then waits for the next one's.
     int st = 0, buf = 0, buf2 = 2;
     auto step = [&](int hh, int q, auto &&work) __attribute__((always_inline)) {
         const bool more = st + 2 < nsteps;
@@ -956,9 +956,10 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_rows, int hq,
 
 // Inputs of the standalone query-sparse backward (and, in the workgroups from
 // prep_blocks on, the zeros of dq, which dQ writes only at the selected rows;
-// one launch, 33 -> 22 us at 8192 of 16384 rows of 8 heads, d = 128): per (selected rank < the
-// device count, head) row, the compact copy of the row of Q and -Delta = -dO . O (O fp32,
-// dO bf16, both compact), written [Hq][cap].  d / 8 lanes per row.
+// at 8192 of 16384 rows of 8 heads, d = 128, 21 us, in two launches 32): per
+// (selected rank < the device count, head) row, the compact copy of the row of
+// Q and -Delta = -dO . O (O fp32, dO bf16, both compact), written [Hq][cap].
+// d / 8 lanes per row.
 template <int D>
 __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq, int64_t cap,
                                                           const int32_t *n_sel_dev,
@@ -966,7 +967,7 @@ __global__ __launch_bounds__(256) void sparse_prep_kernel(int64_t n_rows, int hq
                                                           const uint16_t *q, const float *o,
                                                           const uint16_t *dout, uint16_t *qc,
                                                           float *ndelta, int64_t prep_blocks,
-                                                           float *zero, int64_t n_zero) {
+                                                          float *zero, int64_t n_zero) {
     if (blockIdx.x >= prep_blocks) {
         zero_block(zero, n_zero, blockIdx.x - prep_blocks);
         return;

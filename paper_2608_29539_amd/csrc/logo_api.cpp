@@ -303,14 +303,13 @@ DecodePlan decode_plan(const logo_problem *p, size_t room) {
     // Few caches: shorter chunks while the step has fewer than 1024 work
     // items (four workgroups per CU) and a cache at most 32 chunks, since
     // then a workgroup's serial walk over its keys sets the time.  One cache
-    // of 4K tokens, 32 / 8 heads: 22.6 -> 15.8 us per step with 128-key
-    // chunks (64: 18.1); four of 8K tokens, 8 heads: 27.4 -> 25.3.  Past
-    // that: 16 caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with
-    // shorter ones, one cache of 32K tokens 36.3 with 512 and 44.9 with 256.
-    // (With every cache selected, twice the items of a well filled step cost
-    // more than the shorter walk gives: 16 of 1024 tokens, 32 / 8 heads, 27.3
-    // -> 28.4 us then, 21.4 -> 14.3 with none selected, which the host cannot
-    // tell apart.)
+    // of 4K tokens, 32 / 8 heads: 21.5 us per step, 15.4 with 128-key chunks
+    // (64: 18.1); four of 8K tokens, 8 heads: 27.4, 25.3.  Past that: 16
+    // caches of 4K tokens 33.9 with 512 keys and 36.2-39.1 with shorter ones,
+    // one cache of 32K tokens 36.3 with 512 and 44.9 with 256.  In a well
+    // filled step with every cache selected, twice the items cost more than
+    // the shorter walk gives (16 of 1024 tokens, 32 / 8 heads: 27.3, 28.4 with
+    // 128 keys; with none selected, which the host cannot tell, 21.1, 14.2).
     // Above 512 work items (two workgroups per CU), chunks of more than half
     // of the longest cache are left out: the walk is then hardly shorter and
     // every cache makes a second item (32 caches of 300 tokens, 32 / 8 heads:

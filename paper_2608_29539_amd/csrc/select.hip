@@ -169,7 +169,7 @@ __device__ void permute_lp_head(const LpPrep &p, int head) {
 //
 // Compaction: z = gate > thr in fp32 (NaN never passes, -0 equals +0).  One
 // ballot per slot gives each block's selected count (kept in LDS), one scan
-// of the 512 block counts gives each block's first rank, and a token's rank
+// of the 16 kKeysPerThread block counts gives each block's first rank, and a token's rank
 // adds the selected lanes below it (mbcnt).
 template <bool kThreshold, bool kWrite, int kKeysPerThread>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
@@ -187,10 +187,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int b = blockIdx.y, part = blockIdx.x, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     // Workgroups past the parts copy LP matrices, beside the selection
-    // (which leaves almost every CU free).  Workgroup 0 of the layer launch
-    // did it before, head after head while every other workgroup waited for
-    // its work table: gate projection, transforms and layer at 8192 tokens,
-    // 32 / 8 heads of d = 128, took 551 us then and 336 us now.
+    // (which leaves almost every CU free).  In workgroup 0 of the layer launch,
+    // head after head, the copies hold up every workgroup that waits for its
+    // work table: gate projection, transforms and layer at 8192 tokens, 32 / 8
+    // heads of d = 128, take 550 us there and 322 here.
     if (kWrite && part >= parts) {
         const int h = (part - parts) * B + b;
         if (h < lp.heads)
@@ -462,8 +462,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
             if (lane < kKeysPerThread)
                 hist[lane * kSelWaves + wave] = bc;
             __syncthreads();
-            // exclusive scan of the 512 block counts in token order (block
-            // 16 j + w at hist[16 j + w])
+            // exclusive scan of the block counts in token order (block 16 j + w
+            // at hist[16 j + w])
             constexpr int kBlocks = kKeysPerThread * kSelWaves;
             int chunk_total;
             const int v = tid < kBlocks ? hist[tid] : 0;
