@@ -205,13 +205,15 @@ __device__ __forceinline__ SparseTile split_entry(SparseTile t, int i, int ns, i
 // scans by one workgroup (a layer of 1024 tokens, 4 heads, whose local launch
 // ends with it: 36.7 us with it, 34.5 with this one).  The entries are the
 // general build's, in an order that differs only within its buckets.  Returns
-// false, with nothing written, for larger tables.
+// false for larger tables, with n_tiles and the sequences' first tiles (in
+// l.scratch) for the general build, or -1 for more sequences than it takes.
 template <int NT, int E>
 __device__ bool build_plan_small(const int32_t *cu, int B, const PlanArgs &p,
-                                 plan_detail::PlanLds<E> &l) {
+                                 plan_detail::PlanLds<E> &l, int &n_tiles) {
     using namespace plan_detail;
     static_assert(E >= kSmallPlanTiles && kBuckets >= 2 * kSmallPlanTiles, "LDS of the small plan");
     const int tid = threadIdx.x;
+    n_tiles = -1;
     if (B >= NT || B >= 2 * E)
         return false;
     // tiles per sequence -> exclusive prefix in l.scratch
@@ -226,11 +228,9 @@ __device__ bool build_plan_small(const int32_t *cu, int B, const PlanArgs &p,
         l.total_blocks = 0;
     }
     __syncthreads();
-    const int n_tiles = l.carry;
-    if (n_tiles > kSmallPlanTiles || n_tiles > NT) {
-        __syncthreads();                         // l is rewritten by the general build
+    n_tiles = l.carry;
+    if (n_tiles > kSmallPlanTiles || n_tiles > NT)
         return false;
-    }
     // this thread's tile
     SparseTile t;
     int nb = 0;
@@ -311,16 +311,21 @@ __device__ void build_plan(const int32_t *cu, int B, const PlanArgs &p,
     int32_t *sa = in_lds ? l.scratch : p.scratch;
     int32_t *sb = sa + (in_lds ? E : stride);
     const int tid = threadIdx.x;
-    if (build_plan_small<NT, E>(cu, B, p, l))
+    int n_tiles;
+    if (build_plan_small<NT, E>(cu, B, p, l, n_tiles))
         return;
 
     // 1. tiles per sequence -> exclusive prefix
-    for (int b = tid; b < B; b += NT) {
-        const int s0 = min(cu_sel[b], cap), s1 = min(cu_sel[b + 1], cap);
-        sa[b] = (s1 - s0 + tpw - 1) / tpw;
+    if (n_tiles < 0) {
+        for (int b = tid; b < B; b += NT) {
+            const int s0 = min(cu_sel[b], cap), s1 = min(cu_sel[b + 1], cap);
+            sa[b] = (s1 - s0 + tpw - 1) / tpw;
+        }
+        __syncthreads();
+        n_tiles = scan_array<NT>(sa, B, l.wave_part, &l.carry);
+    } else if (!in_lds && tid < B) {
+        sa[tid] = l.scratch[tid];
     }
-    __syncthreads();
-    const int n_tiles = scan_array<NT>(sa, B, l.wave_part, &l.carry);
     if (tid == 0) {
         sa[B] = n_tiles;
         l.total_blocks = 0;
