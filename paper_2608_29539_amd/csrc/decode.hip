@@ -304,9 +304,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_attn_kernel(const DecodeAr
 // chunk groups x 16 element groups (chunks cg, cg + 4 WPH, ..., D/16 elements
 // in 16-byte loads), so a thread's chain is that share of the chunks; shuffles
 // add a wave's four groups, LDS the waves.  Bound by the latency of that
-// chain: with WPH = 4 the merge of 64 chunks (16 caches of 32K tokens, 32
-// heads of d = 128) takes 6.6 us, with one wave per head and 4-byte loads it
-// took 8.6; with a few chunks per cache the one wave is the faster (a step of
+// chain: with WPH = 4 the merge of 64 chunks (16 caches of 32K tokens, two
+// selected, 32 heads of d = 128) takes 7.4 us, with one wave per head and
+// 4-byte loads 8.7; with a few chunks per cache the one wave is the faster (a step of
 // 64 caches of 2K tokens 82.0 against 84.4 us), so the launcher takes WPH = 4
 // above 16 chunks.  At most 128 chunks per branch.
 constexpr int kMaxChunks = 128;
